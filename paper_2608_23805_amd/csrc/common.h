@@ -82,18 +82,24 @@ struct WorkItem {
     int32_t tile0;     // first tile of this item in the launch's tile space
 };
 
-// Find the item owning tile `t` (items sorted by tile0, tile0[0] == 0).
+// Find the item owning tile `t` (items sorted by tile0, tile0[0] == 0; at most
+// 64 * 64 items).  The wavefront searches 64 ways: lane l reads the first
+// tile of the l-th of 64 equal runs of items, the ballot names the run that
+// holds t, and a second read of that run's items names the item, so the
+// search costs two dependent memory round trips for the 513 items of a
+// 512-expert layer (a binary search: ten, which every tile paid before its
+// first weight load).  All 64 lanes must be active.
 __device__ __forceinline__ int find_item(const WorkItem *items, int n_items, int t)
 {
-    int lo = 0, hi = n_items - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (items[mid].tile0 <= t)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
+    const int lane = threadIdx.x & 63;
+    const int run = (n_items + 63) >> 6;
+    int i = min(lane * run, n_items - 1);
+    // lanes whose run starts past the list repeat its last item: only lanes with lane * run < n_items count
+    const int r0 = __popcll(__ballot(lane * run < n_items && items[i].tile0 <= t)) - 1;
+    if (run == 1)
+        return r0;
+    i = r0 * run + lane;
+    return r0 * run + __popcll(__ballot(lane < run && i < n_items && items[min(i, n_items - 1)].tile0 <= t)) - 1;
 }
 
 // Device-built work list of a decode forward: item i of a launch is the
