@@ -213,6 +213,8 @@ struct KernelSet {
     Geom geom_gu, geom_dn;
     Launch gu_tile, gu_stream, dn_tile, dn_stream;
 };
+// bf16 kernels of a batch of `rows` routed rows (T * K) over E experts
+const KernelSet &bf16_kernels(uint64_t rows, uint64_t E);
 
 // ---- combine / publication and slot generation words (combine.hip)
 // Status word of a forward and where the combine publishes it.

@@ -61,14 +61,11 @@ uint64_t matrix_bytes(uint32_t wdtype, uint64_t rows, uint64_t cols, bool down)
     }
 }
 
-// expert kernels of each storage format
-const KernelSet &kernel_set(uint32_t wdtype)
+// expert kernels of a storage format, for a batch of `rows` routed rows over E experts
+const KernelSet &kernel_set(uint32_t wdtype, uint64_t rows, uint64_t E)
 {
     static const KernelSet f32{tiles_gateup_f32, nullptr, tiles_down_f32, nullptr, nullptr, nullptr,
                                launch_gateup_f32, nullptr, launch_down_f32, nullptr};
-    static const KernelSet bf16{tiles_gateup_tile, tiles_gateup_stream, tiles_down_tile, tiles_down_stream,
-                                geom_gateup_tile, geom_down_tile,
-                                launch_gateup_tile, launch_gateup_stream, launch_down_tile, launch_down_stream};
     static const KernelSet q4{tiles_gateup_q4_tile, tiles_gateup_q4_stream, tiles_down_q4_tile,
                               tiles_down_q4_stream, geom_gateup_q4_tile, geom_down_q4_tile,
                               launch_gateup_q4_tile, launch_gateup_q4_stream, launch_down_q4_tile,
@@ -81,7 +78,7 @@ const KernelSet &kernel_set(uint32_t wdtype)
     case MSI_W_F32: return f32;
     case MSI_W_Q4B32: return q4;
     case MSI_W_KQ: return kq;
-    default: return bf16;
+    default: return bf16_kernels(rows, E);
     }
 }
 
@@ -1053,7 +1050,7 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
                                   hipMemcpyHostToDevice, cs));
             p->res_version[L0] = core.layer_version(L0);
         }
-        const KernelSet &ks = kernel_set(d.wdtype);
+        const KernelSet &ks = kernel_set(d.wdtype, uint64_t(T) * K, E);
         const int tpg = ks.tiles_gu_stream(1, D, I);
         const int tpd = ks.tiles_dn_stream(1, D, I);
         const int has_sh = a->shared_object ? 1 : 0;
@@ -1129,7 +1126,7 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
                                   hipMemcpyHostToDevice, cs));
             p->res_version[L0] = core.layer_version(L0);
         }
-        const KernelSet &ks = kernel_set(d.wdtype);
+        const KernelSet &ks = kernel_set(d.wdtype, uint64_t(T) * K, E);
         const int thr = int(g_stream_threshold);
         const int has_sh = a->shared_object ? 1 : 0;
         WorklistArgs W{};
@@ -1251,7 +1248,7 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
     std::vector<std::vector<Launch>> launches(sched.rounds.size());
     std::vector<WorkItem> table;
     const bool f32 = d.wdtype == MSI_W_F32;
-    const KernelSet &ks = kernel_set(d.wdtype);
+    const KernelSet &ks = kernel_set(d.wdtype, uint64_t(T) * K, E);
     auto add_launch = [&](size_t r, int kind, const std::vector<WorkItem> &items) {
         if (items.empty())
             return;
