@@ -13,9 +13,9 @@
 //    d [rows, cols/256]; q = low | high << 4 and value = d sc_j (q - 32) for
 //    the j-th 16-element sub-block.
 //
-// The k6 integers q - 32 and the k4 integers 128 + q are exact in bf16, so
-// every MFMA partial over a sub-block is a sum of exact products in fp32; the
-// sub-block's scale is then applied in fp32.  The k4 min term takes the
+// The stream path applies each sub-block's scale in fp32: the k6 integers
+// q - 32 and the k4 integers 128 + q are exact in bf16, so every MFMA partial
+// over a sub-block is a sum of exact products.  The k4 min term takes the
 // tokens' sums over the sub-block (one more MFMA, against a fragment of ones)
 // times dmin m_j + 128 d sc_j, which also removes the 128 of the operands.  A
 // 16x16x32 MFMA spans one k4 sub-block, or two k6 sub-blocks: those are split
@@ -25,10 +25,10 @@
 //  * stream path (<= 16 tokens per expert): tokens as the A operand and
 //    weights as the B operand, both read straight from memory, so each output
 //    lane holds one weight row (and that row's coefficients) for four tokens;
-//  * tile path: 128 tokens x 128 weight rows per workgroup, packed weights,
-//    headers and scales staged in LDS (the coefficients decoded once per
-//    stage into fp32), unpacked while the fragments are built.
+//  * tile path: 64 x 128 or 128 x 256 outputs per workgroup, whole
+//    super-blocks summed in units of their d (described there).
 #include "common.h"
+#include "gemm_ring.h"
 #include "kernels.h"
 
 namespace msi {
@@ -38,6 +38,7 @@ namespace {
 constexpr uint32_t BF16_ONE2 = 0x3F803F80u;        // two bf16 1.0
 
 __device__ __forceinline__ float h2f(uint16_t h) { return float(__builtin_bit_cast(_Float16, h)); }
+__device__ __forceinline__ uint16_t f16_bits(float f) { return __builtin_bit_cast(uint16_t, _Float16(f)); }
 
 // 8 unsigned nibbles (element e at bits 4e) -> 8 bf16 values 128 + q, exact
 // (bf16 numbers in [128, 256) are the integers: bits 0x4300 | q).  A partial
@@ -397,303 +398,559 @@ hipError_t launch_down_kq_stream(const ExpertLaunch &L, hipStream_t s)
 }
 
 // ============================================================== tile path
-
+//
+// Integer operands only.  Within a 256-element super-block the accumulators
+// are in units of its d: w / d = sc q (k4, before the min) or sc (q - 32)
+// (k6), exact integers of 10 and 13 bits.
+//   k4: sc q <= 945 is exact in fp16, so one fp16 MFMA per 32 elements.  The
+//       tokens enter as fp16 too: kq_rows_f16_kernel scales each row by a
+//       power of two that puts its largest magnitude in [2^9, 2^10), where
+//       every bf16 value down to 2^-23 of it keeps its 8 bits and smaller
+//       ones are off by at most 2^-34 of it (fp32 sums round at 2^-24).
+//   k6: sc = 16 h + l (h in -8..8, l in -8..7): 16 h (q - 32) and l (q - 32)
+//       have at most 8 significant bits each, two exact bf16 MFMAs.
+// At a super-block's end the k4 accumulators take their mins off, acc -=
+// (dmin / d) sum_j m_j S_j, and both move to the next unit, acc *= d / d_next;
+// the result is acc d after the last (and 2^-k of the row's scale).  S_j, the
+// rows' sums over the 32-element sub-blocks, comes from MFMAs against
+// indicator rows (each wavefront its share of the row blocks), crosses LDS
+// and comes back as an operand in three fp16 parts (33 bits) beside m_j
+// (0..63, exact).  A super-block with d = 0 keeps the previous unit, scale 0.
+//
+// So k4 costs one MFMA per 16 x 16 x 32 block, and k6 two, with the unpacking
+// (13 and 48 vector operations per fragment) shared by MB row blocks and two
+// fp32 operations per output and super-block; applying each sub-block's scale
+// and min in fp32 instead took two (k6: two) FMAs per output and sub-block
+// and kept the vector ALU at 96 cycles a block.
 namespace kqt {
-constexpr int BM = 128, BN = 128, BK = 64, THREADS = 512;
-constexpr int LDA = BK + 8;                 // bf16 elements per staged A row
-constexpr int LDQ = BK / 2 + 4;             // bytes per staged low-nibble row (36: conflict-spread)
-constexpr int LDH = BK / 4 + 4;             // bytes per staged high-part row (k6)
-constexpr int A_BYTES = BM * LDA * 2;
-constexpr int Q_BYTES = BN * LDQ;
-constexpr int H_BYTES = BN * LDH;
-constexpr int S_BYTES = BN * 16;            // four fp32 coefficients per weight row
-constexpr int STAGE = A_BYTES + Q_BYTES + H_BYTES + S_BYTES;
-constexpr size_t LDS_BYTES = size_t(2) * STAGE;
+constexpr int BK = 64, ROWB = BK * 2, QROWB = BK / 2, HROWB = BK / 4;
+
+template <bool GU_, int BM_, int TN_, int WC_, int WPC_>
+struct Shape {
+    static constexpr bool GU = GU_;
+    static constexpr int BM = BM_, TN = TN_, WC = WC_, WPC = WPC_;   // rows, weight rows, wavefronts, workgroups per CU
+    static constexpr int WAVES = WC, THREADS = 64 * WAVES;
+    static constexpr int MB = BM / 16, NB = TN / WC / 16;
+    static constexpr int A_BYTES = BM * ROWB, Q_BYTES = TN * QROWB, H_BYTES = GU ? 0 : TN * HROWB;
+    static constexpr int STAGE = A_BYTES + Q_BYTES + H_BYTES;
+    static constexpr int LA = BM / 8 / WAVES, LQ = TN / 32 / WAVES;   // copies per wavefront per stage
+    static constexpr int NH = TN / 64;                                // copies of high parts per stage (k6)
+    // tables of one super-block (two of each): sub-block scales (k4 [4][TN] pairs of fp16, k6 [16][TN] int8), unit ratios
+    // [TN], min coefficients [TN] and mins [TN][8] fp16 (k4); then the sub-block sums [BM][4][8] fp16 (k4: three
+    // parts, the fourth zero)
+    static constexpr int T_SC = 16 * TN, T_R = TN * 4, T_C = GU ? TN * 4 : 0, T_M = GU ? TN * 16 : 0;
+    static constexpr int TABLE = T_SC + T_R + T_C + T_M;
+    static constexpr int S_BYTES = GU ? BM * 64 : 0;
+    static constexpr size_t LDS = 2 * STAGE + 2 * TABLE + S_BYTES;
+    static_assert(BM % (8 * WAVES) == 0 && TN % (32 * WAVES) == 0 && NH <= WAVES && TN <= THREADS && MB % WC == 0, "");
+    static_assert(LDS * WPC <= 160 * 1024, "");
+};
 }  // namespace kqt
 
-int tiles_gateup_kq_tile(int nrows, int d, int I)
+typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
+
+__device__ __forceinline__ f32x4 mfma16h(const f16x8 &a, const f16x8 &b, const f32x4 &c)
 {
-    (void)d;
-    return ((nrows + kqt::BM - 1) / kqt::BM) * (I / 64);
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
-int tiles_down_kq_tile(int nrows, int d, int I)
+// k4: 8 nibbles and a sub-block's scale (fp16, twice) -> sc q, exact fp16, in the element order 0 4 1 5 2 6 3 7 (the
+// order kq_rows_f16_kernel writes the tokens in): 1024 + q (bits 0x6400 | q) or 1024 + 16 q, then one packed FMA
+// that scales and takes the offset off exactly.
+__device__ __forceinline__ f16x8 unpack_k4_f16(uint32_t w, uint32_t sc2)
 {
-    (void)I;
-    return ((nrows + kqt::BM - 1) / kqt::BM) * (d / kqt::BN);
+    const f16x2 s = __builtin_bit_cast(f16x2, sc2);
+    const f16x2 o = s * f16x2{-1024, -1024}, s16 = s * f16x2{0.0625f16, 0.0625f16}, o16 = s * f16x2{-64, -64};
+    u32x4 r;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t v = w >> (8 * h);
+        const f16x2 a = __builtin_bit_cast(f16x2, (v & 0x000F000Fu) | 0x64006400u);
+        const f16x2 b = __builtin_bit_cast(f16x2, (v & 0x00F000F0u) | 0x64006400u);
+        r[2 * h] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(a, s, o));
+        r[2 * h + 1] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(b, s16, o16));
+    }
+    return __builtin_bit_cast(f16x8, r);
 }
 
-TileGeom geom_gateup_kq_tile(int d, int I)
+// k6: 8 codes and a sub-block's scale -> the two operands
+__device__ __forceinline__ void unpack_k6_pair(uint32_t lo4, uint32_t hi2, int sc, bf16x8 &hi, bf16x8 &lo)
 {
-    (void)d;
-    return TileGeom{kqt::BM, I / 64};
+    const int h16 = (sc + 8) & ~15;                // sc = 16 h + l, l in -8 .. 7
+    uint32_t t = (hi2 | (hi2 << 8)) & 0x00FF00FFu;
+    t = (t | (t << 4)) & 0x0F0F0F0Fu;
+    const uint32_t ev = (lo4 & 0x0F0F0F0Fu) | ((t & 0x03030303u) << 4);          // elements 0, 2, 4, 6
+    const uint32_t od = ((lo4 >> 4) & 0x0F0F0F0Fu) | ((t & 0x0C0C0C0Cu) << 2);   // elements 1, 3, 5, 7
+    const float s1 = float(h16), s2 = float(sc - h16);
+    const float o1 = -32.0f * s1, o2 = -32.0f * s2;
+    u32x4 a, b;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const float fe = float((ev >> (8 * h)) & 0xFFu), fo = float((od >> (8 * h)) & 0xFFu);
+        // exact: integers of at most 8 significant bits, the top half of their binary32
+        a[h] = __builtin_amdgcn_perm(__float_as_uint(fmaf(fo, s1, o1)), __float_as_uint(fmaf(fe, s1, o1)), 0x07060302u);
+        b[h] = __builtin_amdgcn_perm(__float_as_uint(fmaf(fo, s2, o2)), __float_as_uint(fmaf(fe, s2, o2)), 0x07060302u);
+    }
+    hi = __builtin_bit_cast(bf16x8, a);
+    lo = __builtin_bit_cast(bf16x8, b);
 }
 
-TileGeom geom_down_kq_tile(int d, int I)
-{
-    (void)I;
-    return TileGeom{kqt::BM, d / kqt::BN};
-}
-
-// 128 tokens x 128 weight rows per workgroup of eight wavefronts, K in
-// stages of 64 (two 32-element blocks; a stage never crosses a 256-element
-// super-block).  Wavefront (wm, wn), wm in 0..1, wn in 0..3, owns token rows
-// wm*64 .. wm*64+63 and two 16-column blocks: for GATEUP the gate rows
-// nt*64 + wn*16 .. (tile columns wn*16..) and the matching up rows (tile
-// columns 64 + wn*16..), so SiLU * up forms in registers; for down the tile
-// columns wn*32 .. wn*32+31.  Per stage each weight row's coefficients are
-// decoded once into LDS as fp32: gate/up {a0, a1, b0', b1'} (scale d sc_j and
-// folded min dmin m_j + 128 d sc_j of the stage's two blocks), down
-// {s0 .. s3} (d sc_j of its four 16-element sub-blocks).  The k4 min
-// multiplies the tokens' sums over the block, from one MFMA against ones per
-// token block; the k6 sub-blocks are two MFMAs with the other half's weight
-// lanes zeroed.
-template <bool GATEUP>
-__global__ void __launch_bounds__(kqt::THREADS, 1) tile_kq_kernel(ExpertLaunch L)
+// Gate/up: tile columns 0 .. TN/2 - 1 are gate rows nt TN/2 .., the rest the
+// matching up rows; each wavefront owns all MB 16-row blocks and NB column
+// blocks (gate/up: NB / 2 gate blocks and the matching up blocks, so SiLU * up
+// forms in registers).  Weights are the A operand: a lane's outputs are
+// columns 4g .. 4g + 3 of row r16, stored as 16-byte pieces straight to memory.
+// A rows and packed codes are copied straight to LDS, one stage of 64
+// elements ahead (two buffers); thread c < TN reads column c's header one
+// super-block ahead and decodes it into the tables.
+template <class S>
+__global__ void __launch_bounds__(S::THREADS, S::WPC *S::WAVES / 4) tile_kq_kernel(ExpertLaunch L)
 {
     using namespace kqt;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds8[];
+    constexpr bool GU = S::GU;
+    constexpr int BM = S::BM, TN = S::TN, WAVES = S::WAVES, MB = S::MB, NB = S::NB, STAGE = S::STAGE;
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds8[];
     int n_items, n_tiles;
     const int t = launch_tile(L, n_items, n_tiles);
     if (t < 0)
         return;                                   // past the device-built list's tiles
     const WorkItem it = L.items[find_item(L.items, n_items, t)];
-    if (!slot_current(it, L.gen_dev, L.status))
-        return;
+    const uint32_t gnow = slot_gen_now(it, L.gen_dev);   // compared before the stores
     const bool sh = it.slot < 0;
     const int d = L.d, I = L.I;
-    const int K = GATEUP ? d : I;
-    const int ntn = GATEUP ? I / 64 : d / BN;
+    const int K = GU ? d : I;
+    const int ntn = GU ? I / (TN / 2) : d / TN;
     const int local = t - it.tile0;
     const int m0 = (local / ntn) * BM;
     const int nt = local % ntn;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 2, wn = wave & 3;
+    const int valid = min(BM, it.nrows - m0);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (uniform: copy destinations and resources)
+    const int r16 = lane & 15, g = lane >> 4;
 
-    const uint16_t *abase = reinterpret_cast<const uint16_t *>(GATEUP ? L.x : (sh ? L.act_s : L.act));
-    const int32_t *perm = (GATEUP && !sh) ? L.perm : nullptr;
     const uint8_t *obj = sh ? L.shared_w : L.wbase + uint64_t(it.slot) * L.wstride;
     const uint32_t mbytes = k4_bytes(I, d);
+    // byte offset, from the object, of tile column c's matrix and its row there
+    auto col_matrix = [&](int c) -> uint32_t { return GU ? (c < TN / 2 ? 0u : mbytes) : 2 * mbytes; };
+    auto col_row = [&](int c) -> uint32_t {
+        return GU ? uint32_t(nt * (TN / 2) + (c < TN / 2 ? c : c - TN / 2)) : uint32_t(nt * TN + c);
+    };
 
-    // A: 128 rows x 64 bf16 per stage = 8 chunks of 16 B per row; 2 per thread
-    uint32_t aoff[2];
+    // ---- stage copies (slots permuted as in the 4-bit tiles, so fragment reads are free of bank conflicts)
+    [[maybe_unused]] const void *abase = GU ? L.xh
+                           : static_cast<const uint8_t *>(sh ? L.act_s : L.act) + (int64_t(it.row0) + m0) * int64_t(I) * 2;
+    uint32_t aoff[S::LA], qoff[S::LQ], hoff = 0;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int r = (tid >> 3) + 64 * i;
-        int64_t src = 0;
-        if (m0 + r < it.nrows)
-            src = perm ? int64_t(perm[it.row0 + m0 + r]) : int64_t(it.row0 + m0 + r);
-        aoff[i] = uint32_t(src * K) + (tid & 7) * 8;
+    for (int i = 0; i < S::LA; ++i) {
+        const int r = 8 * (WAVES * i + wave) + (lane >> 3);
+        const int m = m0 + min(r, valid - 1);     // rows past the end repeat the last one and are never stored
+        const uint32_t src = !GU ? uint32_t(m - m0) : sh ? uint32_t(it.row0 + m) : uint32_t(L.perm[it.row0 + m]);
+        aoff[i] = src * uint32_t(K * 2) + uint32_t(((lane & 7) ^ ((r >> 1) & 7)) << 4);
     }
-    auto weight_row = [&](int c) -> int {          // tile column -> row of its matrix
-        if (GATEUP)
-            return nt * 64 + (c & 63);
-        return nt * BN + c;
-    };
-    auto matrix_of = [&](int c) -> const uint8_t * {
-        if (GATEUP)
-            return obj + (c < 64 ? 0u : mbytes);
-        return obj + 2 * mbytes;
-    };
-    // threads 0..255: low nibbles, 128 rows x 32 B per stage, 2 chunks of 16 B per row;
-    // threads 256..383: tile column tid - 256's header (gate/up) or high parts (down);
-    // threads 384..511: tile column tid - 384's sub-block scales (down)
-    const int role = tid >> 7;                      // 0, 1: nibbles; 2: header / high parts; 3: scales
-    const int brow_l = (tid & 255) >> 1, bchunk = tid & 1;
-    const uint8_t *qrow = matrix_of(brow_l) + int64_t(weight_row(brow_l)) * (K / 2) + bchunk * 16;
-    const int cc = tid & 127;
-    const uint8_t *cmat = matrix_of(cc);
-    const int64_t crow = weight_row(cc);
-    const int rows_m = GATEUP ? I : d;
-    const u32x4 *hdr = reinterpret_cast<const u32x4 *>(cmat + uint32_t(rows_m) * uint32_t(K / 2)) + crow * (K / 256);
-    const K6Planes P = k6_planes(cmat, rows_m, K);
-
-    // the 16-byte word of roles 0..2 (nibbles, header or high parts) goes through one register
-    // quadruple, loaded from a per-role address
-    u32x4 ra[2], rw;
-    uint32_t rsc = 0;
-    uint16_t rd = 0;
-    auto load = [&](int k0) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            ra[i] = *reinterpret_cast<const u32x4 *>(abase + (aoff[i] + uint32_t(k0)));
-        if (role < 3) {
-            const u32x4 *src = role < 2 ? reinterpret_cast<const u32x4 *>(qrow + k0 / 2)
-                               : GATEUP ? hdr + k0 / 256
-                                        : reinterpret_cast<const u32x4 *>(P.qh + crow * (K / 4) + k0 / 4);
-            rw = *src;
-        } else if (!GATEUP) {
-            rsc = *reinterpret_cast<const uint32_t *>(P.sc + crow * (K / 16) + k0 / 16);
-            rd = P.d[crow * (K / 256) + k0 / 256];
-        }
-    };
-    auto store = [&](int buf, int k0) {
+    for (int i = 0; i < S::LQ; ++i) {
+        const int c = 32 * (WAVES * i + wave) + (lane >> 1);
+        qoff[i] = col_matrix(c) + col_row(c) * uint32_t(K / 2) + uint32_t(16 * ((lane & 1) ^ ((c >> 3) & 1)));
+    }
+    if (!GU)
+        hoff = col_matrix(0) + uint32_t(d) * uint32_t(K / 2) + col_row(64 * (wave % S::NH) + lane) * uint32_t(K / 4);
+    auto issue = [&](int stage, int buf) {
         uint8_t *st = lds8 + buf * STAGE;
-        uint16_t *a = reinterpret_cast<uint16_t *>(st);
+#if defined(__HIP_DEVICE_COMPILE__)
+        const __amdgpu_buffer_rsrc_t ar =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(abase), 0, 0x7fffffff, 0x00020000u);
+        const __amdgpu_buffer_rsrc_t wr_ =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(obj), 0, 0x7fffffff, 0x00020000u);
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            *reinterpret_cast<u32x4 *>(a + ((tid >> 3) + 64 * i) * LDA + (tid & 7) * 8) = ra[i];
-        float *cfp = reinterpret_cast<float *>(st + A_BYTES + Q_BYTES + H_BYTES + cc * 16);
-        if (role < 2) {
-            uint32_t *q = reinterpret_cast<uint32_t *>(st + A_BYTES + brow_l * LDQ + bchunk * 16);
+        for (int i = 0; i < S::LA; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ar, (lds_void_t *)(st + (WAVES * i + wave) * 1024), 16, aoff[i],
+                                                     stage * ROWB, 0, 0);
 #pragma unroll
-            for (int w = 0; w < 4; ++w)
-                q[w] = rw[w];
-        } else if (role == 2) {
-            if (GATEUP) {
-                const int j0 = (k0 & 255) >> 5;
-                float a0, b0, a1, b1;
-                k4_coef128(rw, j0, a0, b0);
-                k4_coef128(rw, j0 + 1, a1, b1);
-                *reinterpret_cast<f32x4 *>(cfp) = f32x4{a0, a1, b0, b1};
-            } else {
-                uint32_t *h = reinterpret_cast<uint32_t *>(st + A_BYTES + Q_BYTES + cc * LDH);
-#pragma unroll
-                for (int w = 0; w < 4; ++w)
-                    h[w] = rw[w];
-            }
-        } else if (!GATEUP) {
-            const float dv = h2f(rd);
-            f32x4 cf;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                cf[k] = dv * float(int(int8_t((rsc >> (8 * k)) & 0xFFu)));
-            *reinterpret_cast<f32x4 *>(cfp) = cf;
-        }
+        for (int i = 0; i < S::LQ; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr_, (lds_void_t *)(st + S::A_BYTES + (WAVES * i + wave) * 1024),
+                                                     16, qoff[i], stage * QROWB, 0, 0);
+        if (!GU && wave < S::NH)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr_, (lds_void_t *)(st + S::A_BYTES + S::Q_BYTES + wave * 1024), 16,
+                                                     hoff, stage * HROWB, 0, 0);
+#else
+        (void)st, (void)stage;
+#endif
     };
 
-    f32x4 acc[4][2];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-            acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int r16 = lane & 15, g = lane >> 4;
-    auto col_of = [&](int nb) -> int {              // tile column block of this wavefront
-        if (GATEUP)
-            return nb * 64 + wn * 16;
-        return wn * 32 + nb * 16;
+    // ---- super-block tables
+    uint8_t *tables = lds8 + 2 * STAGE;
+    uint16_t *sums = reinterpret_cast<uint16_t *>(lds8 + 2 * STAGE + 2 * S::TABLE);
+    const int nsb = K / 256;
+    u32x4 hd = {0u, 0u, 0u, 0u};                  // next super-block's header (k6: its 16 scales)
+    uint16_t hd6 = 0;                             // k6: its d
+    float unit = 1.0f;                            // d of the last decoded super-block
+    const uint8_t *hp = nullptr;
+    const uint16_t *dp = nullptr;
+    if (tid < TN) {
+        const uint8_t *mat = obj + col_matrix(tid);
+        const uint32_t row = col_row(tid);
+        if (GU) {
+            hp = mat + uint32_t(I) * uint32_t(K / 2) + row * uint32_t(nsb) * 16u;
+        } else {
+            const K6Planes P = k6_planes(mat, uint32_t(d), uint32_t(K));
+            hp = reinterpret_cast<const uint8_t *>(P.sc) + row * uint32_t(K / 16);
+            dp = P.d + row * uint32_t(nsb);
+        }
+    }
+    auto load_header = [&](int sb) {
+        if (tid < TN) {
+            hd = *reinterpret_cast<const u32x4 *>(hp + 16 * sb);
+            if (!GU)
+                hd6 = dp[sb];
+        }
     };
-    const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{BF16_ONE2, BF16_ONE2, BF16_ONE2, BF16_ONE2});
-    const bf16x8 zero = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-    const bool first_half = g < 2;                  // B lanes of elements 0 .. 15 of a block
-    auto compute = [&](int buf) {
+    auto decode_header = [&](int sb) {
+        if (tid >= TN)
+            return;
+        uint8_t *tb = tables + (sb & 1) * S::TABLE;
+        const float dv = h2f(GU ? uint16_t(hd[0]) : hd6);
+        const float u = dv != 0.0f ? dv : unit;
+        if constexpr (GU) {
+            // pairs of 6-bit values -> pairs of fp16, exact through 1024 + v
+            auto pair = [](uint32_t v12) {
+                const uint32_t b = (v12 & 63u) | ((v12 & 0xFC0u) << 10) | 0x64006400u;
+                return __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, b) - f16x2{1024, 1024});
+            };
+            const uint32_t m3 = __builtin_amdgcn_alignbit(hd[3], hd[2], 16);   // mins 0 ..: bits 0 .. 31 of their 48
+            const uint32_t v[8] = {hd[1],        hd[1] >> 12, __builtin_amdgcn_alignbit(hd[2], hd[1], 24), hd[2] >> 4,
+                                   m3,           m3 >> 12,    hd[3] >> 8,                                  hd[3] >> 20};
+            uint32_t p[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                p[j] = pair(v[j]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                reinterpret_cast<uint32_t *>(tb)[j * TN + tid] = dv != 0.0f ? p[j] : 0u;
+            *reinterpret_cast<u32x4 *>(tb + S::T_SC + S::T_R + S::T_C + tid * 16) = u32x4{p[4], p[5], p[6], p[7]};
+            reinterpret_cast<float *>(tb + S::T_SC + S::T_R)[tid] = h2f(uint16_t(hd[0] >> 16)) / u;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const uint32_t b = (hd[j >> 2] >> (8 * (j & 3))) & 0xFFu;
+                tb[j * TN + tid] = dv != 0.0f ? uint8_t(b) : uint8_t(0);
+            }
+        }
+        reinterpret_cast<float *>(tb + S::T_SC)[tid] = unit / u;
+        unit = u;
+    };
+
+    auto col_of = [&](int nb) -> int {              // tile column block of this wavefront
+        if (GU)
+            return nb < NB / 2 ? (wave * (NB / 2) + nb) * 16 : TN / 2 + (wave * (NB / 2) + nb - NB / 2) * 16;
+        return (wave * NB + nb) * 16;
+    };
+    f32x4 acc[NB][MB];
+#pragma unroll
+    for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int b = 0; b < MB; ++b)
+            acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // sub-block sums: this wavefront's share of its row blocks
+    constexpr int SMB = GU ? MB / S::WC : 1;
+    f32x4 sacc[SMB];
+    auto compute = [&](int buf, int stage) {
         const uint8_t *st = lds8 + buf * STAGE;
-        const uint16_t *a = reinterpret_cast<const uint16_t *>(st);
-        const uint8_t *q = st + A_BYTES;
-        const uint8_t *h = st + A_BYTES + Q_BYTES;
-        const float *cf = reinterpret_cast<const float *>(st + A_BYTES + Q_BYTES + H_BYTES);
+        const uint8_t *sct = tables + ((stage >> 2) & 1) * S::TABLE;
 #pragma unroll
         for (int kb = 0; kb < BK / 32; ++kb) {
-            bf16x8 af[4];
+            [[maybe_unused]] const int jb = (stage & 3) * 2 + kb;    // 32-element block of the super-block
+            u32x4 af[MB];
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
-                af[mb] = as_bf16x8(*reinterpret_cast<const u32x4 *>(a + (wm * 64 + mb * 16 + r16) * LDA + kb * 32 + g * 8));
-            if (GATEUP) {
-                f32x4 sx[4];                        // tokens' sums over the block
+            for (int mb = 0; mb < MB; ++mb) {
+                const int r = mb * 16 + r16;
+                af[mb] = *reinterpret_cast<const u32x4 *>(st + r * ROWB + (((4 * kb + g) ^ ((r >> 1) & 7)) << 4));
+            }
+            if constexpr (GU) {
+                const uint32_t one = r16 == jb ? 0x3C003C00u : 0u;
+                const f16x8 ind = __builtin_bit_cast(f16x8, u32x4{one, one, one, one});
 #pragma unroll
-                for (int mb = 0; mb < 4; ++mb)
-                    sx[mb] = mfma16(af[mb], ones, f32x4{0.f, 0.f, 0.f, 0.f});
+                for (int q = 0; q < SMB; ++q) {
+                    const int r = (wave * SMB + q) * 16 + r16;
+                    const f16x8 a = *reinterpret_cast<const f16x8 *>(st + r * ROWB + (((4 * kb + g) ^ ((r >> 1) & 7)) << 4));
+                    sacc[q] = mfma16h(ind, a, sacc[q]);
+                }
+            }
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    const int c = col_of(nb) + r16;                // B fragment: weight row c
-                    const bf16x8 bq = unpack_u4_128(*reinterpret_cast<const uint32_t *>(q + c * LDQ + kb * 16 + g * 4));
-                    const float sa = cf[c * 4 + kb], sb = cf[c * 4 + 2 + kb];   // output column = c
+            for (int nb = 0; nb < NB; ++nb) {
+                const int c = col_of(nb) + r16;                    // A fragment: weight row c
+                const uint32_t cw = *reinterpret_cast<const uint32_t *>(st + S::A_BYTES + c * QROWB +
+                                                                        16 * (kb ^ ((c >> 3) & 1)) + 4 * g);
+                if constexpr (GU) {
+                    const uint32_t s2 = reinterpret_cast<const uint32_t *>(sct)[(stage & 3) * TN + c];
+                    const f16x8 w = unpack_k4_f16(cw, __builtin_amdgcn_perm(s2, s2, kb ? 0x03020302u : 0x01000100u));
 #pragma unroll
-                    for (int mb = 0; mb < 4; ++mb) {
-                        const f32x4 part = mfma16(af[mb], bq, f32x4{0.f, 0.f, 0.f, 0.f});
+                    for (int mb = 0; mb < MB; ++mb)
+                        acc[nb][mb] = mfma16h(w, __builtin_bit_cast(f16x8, af[mb]), acc[nb][mb]);
+                } else {
+                    const uint32_t hw = *reinterpret_cast<const uint16_t *>(st + S::A_BYTES + S::Q_BYTES + c * HROWB +
+                                                                            8 * kb + 2 * g);
+                    bf16x8 w1, w2;
+                    unpack_k6_pair(cw, hw, int(int8_t(sct[(2 * jb + (g >> 1)) * TN + c])), w1, w2);
 #pragma unroll
-                        for (int rr = 0; rr < 4; ++rr) {
-                            acc[mb][nb][rr] = fmaf(sa, part[rr], acc[mb][nb][rr]);
-                            acc[mb][nb][rr] = fmaf(-sb, sx[mb][rr], acc[mb][nb][rr]);
+                    for (int mb = 0; mb < MB; ++mb)
+                        acc[nb][mb] = mfma16(w1, as_bf16x8(af[mb]), acc[nb][mb]);
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+                        acc[nb][mb] = mfma16(w2, as_bf16x8(af[mb]), acc[nb][mb]);
+                }
+            }
+        }
+    };
+    auto clear_sums = [&]() {
+#pragma unroll
+        for (int q = 0; q < SMB; ++q)
+            sacc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    // a lane holds sub-blocks 4g .. 4g + 3 (g < 2) of row r16: their three fp16 parts, in the operand's layout
+    auto store_sums = [&]() {
+        if constexpr (GU) {
+            if (g < 2) {
+#pragma unroll
+                for (int q = 0; q < SMB; ++q) {
+                    uint16_t *sp = sums + ((wave * SMB + q) * 16 + r16) * 32 + 4 * g;
+                    f32x4 s = sacc[q];
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) {
+                        uint16_t h[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            h[i] = f16_bits(s[i]);
+                            s[i] -= h2f(h[i]);
                         }
+                        *reinterpret_cast<uint2 *>(sp + 8 * p) =
+                            make_uint2(uint32_t(h[0]) | (uint32_t(h[1]) << 16), uint32_t(h[2]) | (uint32_t(h[3]) << 16));
                     }
+                }
+            }
+        }
+    };
+    // super-block sb - 1 ends: its mins come off, and the accumulators move to super-block sb's unit
+    auto finish = [&](int sb) {
+        const uint8_t *tb = tables + (sb & 1) * S::TABLE, *to = tables + ((sb & 1) ^ 1) * S::TABLE;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const f32x4 r = *reinterpret_cast<const f32x4 *>(tb + S::T_SC + (col_of(nb) + 4 * g) * 4);
+            if constexpr (GU) {
+                const f16x8 mf =
+                    *reinterpret_cast<const f16x8 *>(to + S::T_SC + S::T_R + S::T_C + (col_of(nb) + r16) * 16);
+                f32x4 cm = *reinterpret_cast<const f32x4 *>(to + S::T_SC + S::T_R + (col_of(nb) + 4 * g) * 4);
+                cm = cm * r;
+#pragma unroll
+                for (int m0_ = 0; m0_ < MB; m0_ += 2) {
+                    __builtin_amdgcn_sched_barrier(0);   // (two row blocks at a time: hoisted reads would spill)
+                    f32x4 m[2];
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const f16x8 pa = *reinterpret_cast<const f16x8 *>(
+                            sums + ((m0_ + q) * 16 + r16) * 32 + 8 * g);
+                        m[q] = mfma16h(mf, pa, f32x4{0.f, 0.f, 0.f, 0.f});
+                    }
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            acc[nb][m0_ + q][i] = fmaf(-cm[i], m[q][i], acc[nb][m0_ + q][i] * r[i]);
                 }
             } else {
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    const int c = col_of(nb) + r16;
-                    const bf16x8 w = unpack_k6(*reinterpret_cast<const uint32_t *>(q + c * LDQ + kb * 16 + g * 4),
-                                               *reinterpret_cast<const uint16_t *>(h + c * LDH + kb * 8 + g * 2));
-                    const bf16x8 w0 = first_half ? w : zero, w1 = first_half ? zero : w;
-                    const float s0 = cf[c * 4 + 2 * kb], s1 = cf[c * 4 + 2 * kb + 1];
+                for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                    for (int mb = 0; mb < 4; ++mb) {
-                        const f32x4 p0 = mfma16(af[mb], w0, f32x4{0.f, 0.f, 0.f, 0.f});
-                        const f32x4 p1 = mfma16(af[mb], w1, f32x4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-                        for (int rr = 0; rr < 4; ++rr) {
-                            acc[mb][nb][rr] = fmaf(s0, p0[rr], acc[mb][nb][rr]);
-                            acc[mb][nb][rr] = fmaf(s1, p1[rr], acc[mb][nb][rr]);
-                        }
-                    }
-                }
+                    for (int i = 0; i < 4; ++i)
+                        acc[nb][mb][i] *= r[i];
             }
         }
     };
 
     const int nk = K / BK;
-    load(0);
-    store(0, 0);
-    if (nk > 1)
-        load(BK);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        compute(kt & 1);
-        if (kt + 1 < nk)
-            store((kt + 1) & 1, (kt + 1) * BK);
-        if (kt + 2 < nk)
-            load((kt + 2) * BK);
-        __syncthreads();
+    if (GU)
+        for (int r = tid; r < BM; r += S::THREADS)
+            *reinterpret_cast<u32x4 *>(sums + r * 32 + 24) = u32x4{0u, 0u, 0u, 0u};
+    load_header(0);
+    issue(0, 0);
+    decode_header(0);
+    for (int sb = 0; sb < nsb; ++sb) {
+        if (sb + 1 < nsb)
+            load_header(sb + 1);
+        clear_sums();
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q) {
+            const int kt = 4 * sb + q;
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0x0070);     // vmcnt(0) lgkmcnt(0): this stage and the tables are in LDS
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (kt + 1 < nk)
+                issue(kt + 1, (kt + 1) & 1);
+            compute(kt & 1, kt);
+        }
+        store_sums();
+        if (sb + 1 < nsb)
+            decode_header(sb + 1);
+        else if (tid < TN)                          // after the last, the unit is 1
+            reinterpret_cast<float *>(tables + (nsb & 1) * S::TABLE + S::T_SC)[tid] = unit;
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0): the sums and the tables (stage copies stay in flight)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        finish(sb + 1);
     }
+    if (!slot_gen_ok(it, gnow, L.status))
+        return;
 
-    // lane holds rows 4g + rr of each 16x16 block, column r16
+    // ---- epilogue: lane holds columns 4g .. 4g + 3 of each block of row r16; two blocks at a time are regrouped
+    // so that each lane stores 16 contiguous bytes
+    const int64_t rowbase = int64_t(it.row0) + m0;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < MB; ++mb) {
+        const int row = mb * 16 + r16;
+        const bool in = row < valid;
+        constexpr int OB = GU ? NB / 2 : NB;        // output blocks
+        uint32_t lo[OB], hi[OB];
+        if constexpr (GU) {
+            const int k = in ? -int(L.xexp[sh ? it.row0 + m0 + row : L.perm[it.row0 + m0 + row]]) : 0;
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const int row = wm * 64 + mb * 16 + 4 * g + rr;
-            if (m0 + row >= it.nrows)
-                continue;
-            const int64_t orow = int64_t(it.row0) + m0 + row;
-            if (GATEUP) {
-                uint16_t *act = reinterpret_cast<uint16_t *>(sh ? L.act_s : L.act) + orow * I;
-                act[nt * 64 + wn * 16 + r16] = f32_to_bf16(silu(acc[mb][0][rr]) * acc[mb][1][rr]);
-            } else {
-                uint16_t *y = static_cast<uint16_t *>(sh ? L.ys : L.y) + orow * d;
-                const float w = sh ? 1.0f : L.row_weight[orow];
+            for (int nb = 0; nb < OB; ++nb) {
+                float v[4];
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb)
-                    y[nt * BN + wn * 32 + nb * 16 + r16] = f32_to_bf16(acc[mb][nb][rr] * w);
+                for (int i = 0; i < 4; ++i)
+                    v[i] = silu_hw(ldexpf(acc[nb][mb][i], k)) * ldexpf(acc[nb + OB][mb][i], k);
+                lo[nb] = pack_bf16x2_hw(v[0], v[1]);
+                hi[nb] = pack_bf16x2_hw(v[2], v[3]);
+            }
+        } else {
+            const float w = (sh || !in) ? 1.0f : L.row_weight[rowbase + row];
+#pragma unroll
+            for (int nb = 0; nb < OB; ++nb) {
+                lo[nb] = pack_bf16x2_hw(acc[nb][mb][0] * w, acc[nb][mb][1] * w);
+                hi[nb] = pack_bf16x2_hw(acc[nb][mb][2] * w, acc[nb][mb][3] * w);
             }
         }
+        uint16_t *dst = GU ? static_cast<uint16_t *>(sh ? L.act_s : L.act) + (rowbase + row) * I + nt * (TN / 2)
+                           : static_cast<uint16_t *>(sh ? L.ys : L.y) + (rowbase + row) * d + nt * TN;
+        dst += wave * OB * 16;
+        if constexpr (OB == 1) {
+            if (in)
+                *reinterpret_cast<uint2 *>(dst + 4 * g) = make_uint2(lo[0], hi[0]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < OB / 2; ++k) {
+                const uint4 v = gather16(lo[2 * k], hi[2 * k], lo[2 * k + 1], hi[2 * k + 1]);
+                if (in)
+                    *reinterpret_cast<uint4 *>(dst + 32 * k + 8 * g) = v;
+            }
+        }
+    }
 }
 
-hipError_t launch_gateup_kq_tile(const ExpertLaunch &L, hipStream_t s)
+// Tokens for the k4 tiles: xh[t] = fp16(2^k x[t]) with elements 0 4 1 5 2 6 3 7 of each group of eight, k = xexp[t]
+// putting the row's largest magnitude in [2^9, 2^10) (0 for rows of zeros or with an infinity or NaN; at most
+// 127).  One wavefront per row; the row is read twice, the second time from the caches.
+__global__ void __launch_bounds__(256) kq_rows_f16_kernel(const uint16_t *__restrict__ x, uint16_t *__restrict__ xh,
+                                                          int8_t *__restrict__ xexp, int T, int d)
 {
-    if (L.n_tiles == 0)
+    const int t = int(blockIdx.x) * 4 + int(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (t >= T)
+        return;
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(x + int64_t(t) * d);
+    u32x4 *dst = reinterpret_cast<u32x4 *>(xh + int64_t(t) * d);
+    uint32_t m = 0;
+    for (int c = lane; c < d / 8; c += 64) {
+        const u32x4 v = src[c];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            m = max(m, max(v[i] & 0x7FFFu, (v[i] >> 16) & 0x7FFFu));
+    }
+    // (magnitudes of bf16 bits order as integers; up to 0x7FFF they are exact as floats)
+    m = uint32_t(wave_max(float(m)));
+    const int e = max(int(m >> 7), 1);
+    const int k = (m == 0u || e == 255) ? 0 : min(136 - e, 127);
+    for (int c = lane; c < d / 8; c += 64) {
+        const u32x4 v = src[c];
+        uint16_t h[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            h[2 * i] = f16_bits(ldexpf(__uint_as_float(v[i] << 16), k));
+            h[2 * i + 1] = f16_bits(ldexpf(__uint_as_float(v[i] & 0xFFFF0000u), k));
+        }
+        dst[c] = u32x4{uint32_t(h[0]) | (uint32_t(h[4]) << 16), uint32_t(h[1]) | (uint32_t(h[5]) << 16),
+                       uint32_t(h[2]) | (uint32_t(h[6]) << 16), uint32_t(h[3]) | (uint32_t(h[7]) << 16)};
+    }
+    if (lane == 0)
+        xexp[t] = int8_t(k);
+}
+
+hipError_t launch_kq_rows_f16(const void *x, void *xh, int8_t *xexp, int T, int d, hipStream_t s)
+{
+    if (T == 0)
         return hipSuccess;
-    if (L.d % 256 != 0 || L.I % 64 != 0)
-        return hipErrorInvalidValue;
-    launch_k(tile_kq_kernel<true>, L.n_tiles, kqt::THREADS, kqt::LDS_BYTES, s, L);
+    launch_k(kq_rows_f16_kernel, unsigned((T + 3) / 4), 256, 0, s, static_cast<const uint16_t *>(x),
+             static_cast<uint16_t *>(xh), xexp, T, d);
     return hipGetLastError();
 }
 
-hipError_t launch_down_kq_tile(const ExpertLaunch &L, hipStream_t s)
+namespace {
+
+template <class S>
+int kq_tiles(int nrows, int d, int I)
+{
+    return (nrows + S::BM - 1) / S::BM * (S::GU ? I / (S::TN / 2) : d / S::TN);
+}
+
+template <class S>
+TileGeom kq_geom(int d, int I)
+{
+    return TileGeom{S::BM, S::GU ? I / (S::TN / 2) : d / S::TN};
+}
+
+template <class S>
+hipError_t launch_kq_tile(const ExpertLaunch &L, hipStream_t s)
 {
     if (L.n_tiles == 0)
         return hipSuccess;
-    if (L.I % 256 != 0 || L.d % kqt::BN != 0)
+    if (L.d % 256 != 0 || L.I % 256 != 0)
         return hipErrorInvalidValue;
-    launch_k(tile_kq_kernel<false>, L.n_tiles, kqt::THREADS, kqt::LDS_BYTES, s, L);
+    launch_k(tile_kq_kernel<S>, L.n_tiles, S::THREADS, S::LDS, s, L);
     return hipGetLastError();
+}
+
+template <bool GU>
+using KqSmall = kqt::Shape<GU, 64, 128, 4, 3>;
+template <bool GU>
+using KqBig = kqt::Shape<GU, 128, 256, 4, 2>;
+
+template <template <bool> class S>
+const KernelSet kq_set{kq_tiles<S<true>>, tiles_gateup_kq_stream, kq_tiles<S<false>>, tiles_down_kq_stream,
+                       kq_geom<S<true>>, kq_geom<S<false>>,
+                       launch_kq_tile<S<true>>, launch_gateup_kq_stream,
+                       launch_kq_tile<S<false>>, launch_down_kq_stream};
+
+}  // namespace
+
+// The tile form by the mean rows per expert; the two are bit-identical (the
+// same chain of operations per output), so the choice is the launch's.
+// Measured (MI355X, E 512, d 2048, I 512, K 10; gate/up + down, us):
+//   mean rows   64 x 128   128 x 256   (per-sub-block scaling, 128 x 128)
+//      20       182+135    284+206        526+413
+//      59       300+230    365+275           -
+//      80       443+344    377+284        732+642
+//     640      2431+1917  1906+1534      4134+3573
+const KernelSet &kq_kernels(uint64_t rows, uint64_t E)
+{
+    return rows <= 64 * E ? kq_set<KqSmall> : kq_set<KqBig>;
 }
 
 hipError_t init_kq_attributes()
 {
-    const void *ks[] = {reinterpret_cast<const void *>(&tile_kq_kernel<true>),
-                        reinterpret_cast<const void *>(&tile_kq_kernel<false>)};
-    for (const void *k : ks) {
+    for (const void *k : {reinterpret_cast<const void *>(&tile_kq_kernel<KqSmall<true>>),
+                          reinterpret_cast<const void *>(&tile_kq_kernel<KqSmall<false>>),
+                          reinterpret_cast<const void *>(&tile_kq_kernel<KqBig<true>>),
+                          reinterpret_cast<const void *>(&tile_kq_kernel<KqBig<false>>)}) {
         const hipError_t e = allow_large_lds(k);
         if (e != hipSuccess)
             return e;

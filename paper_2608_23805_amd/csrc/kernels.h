@@ -89,6 +89,8 @@ struct ExpertLaunch {
     int n_items;
     int n_tiles;
     const void *x;               // [T, d] hidden states (bf16 or f32)
+    const void *xh;              // quantized mix, tile path: the hidden states as scaled fp16 and
+    const int8_t *xexp;          // their rows' exponents (launch_kq_rows_f16)
     const int32_t *perm;         // gather map of routed rows
     const uint8_t *wbase;        // slot pool
     uint64_t wstride;
@@ -191,14 +193,10 @@ hipError_t init_q4_attributes();
 // quantized-expert mix, Wg / Wu in k4 and Wd in k6 (experts_kq.hip)
 int tiles_gateup_kq_stream(int nrows, int d, int I);
 int tiles_down_kq_stream(int nrows, int d, int I);
-int tiles_gateup_kq_tile(int nrows, int d, int I);
-int tiles_down_kq_tile(int nrows, int d, int I);
-TileGeom geom_gateup_kq_tile(int d, int I);
-TileGeom geom_down_kq_tile(int d, int I);
 hipError_t launch_gateup_kq_stream(const ExpertLaunch &L, hipStream_t s);
 hipError_t launch_down_kq_stream(const ExpertLaunch &L, hipStream_t s);
-hipError_t launch_gateup_kq_tile(const ExpertLaunch &L, hipStream_t s);
-hipError_t launch_down_kq_tile(const ExpertLaunch &L, hipStream_t s);
+// xh[t] = fp16(2^xexp[t] x[t]) in the k4 tiles' element order
+hipError_t launch_kq_rows_f16(const void *x, void *xh, int8_t *xexp, int T, int d, hipStream_t s);
 hipError_t init_kq_attributes();
 
 // The expert kernels of one storage format: the tile path (rows above the
@@ -213,7 +211,8 @@ struct KernelSet {
     Geom geom_gu, geom_dn;
     Launch gu_tile, gu_stream, dn_tile, dn_stream;
 };
-// bf16 kernels of a batch of `rows` routed rows (T * K) over E experts
+// kernels of a batch of `rows` routed rows (T * K) over E experts
+const KernelSet &kq_kernels(uint64_t rows, uint64_t E);
 const KernelSet &bf16_kernels(uint64_t rows, uint64_t E);
 
 // ---- combine / publication and slot generation words (combine.hip)

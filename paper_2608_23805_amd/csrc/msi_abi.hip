@@ -70,14 +70,10 @@ const KernelSet &kernel_set(uint32_t wdtype, uint64_t rows, uint64_t E)
                               tiles_down_q4_stream, geom_gateup_q4_tile, geom_down_q4_tile,
                               launch_gateup_q4_tile, launch_gateup_q4_stream, launch_down_q4_tile,
                               launch_down_q4_stream};
-    static const KernelSet kq{tiles_gateup_kq_tile, tiles_gateup_kq_stream, tiles_down_kq_tile,
-                              tiles_down_kq_stream, geom_gateup_kq_tile, geom_down_kq_tile,
-                              launch_gateup_kq_tile, launch_gateup_kq_stream, launch_down_kq_tile,
-                              launch_down_kq_stream};
     switch (wdtype) {
     case MSI_W_F32: return f32;
     case MSI_W_Q4B32: return q4;
-    case MSI_W_KQ: return kq;
+    case MSI_W_KQ: return kq_kernels(rows, E);
     default: return bf16_kernels(rows, E);
     }
 }
@@ -203,6 +199,7 @@ struct msi_plan {
     bool status_clean = true;           // status_dev is zero (the last forward's combine cleared it)
     uint32_t *tail_host = nullptr;      // pinned [2 + E]: status | DONE, demanded count, ids (written by the combine)
     uint32_t *tail_hdev = nullptr;      // device-visible address of tail_host
+    int8_t *xexp_dev = nullptr;         // MSI_W_KQ: exponents of the tile path's fp16 tokens [2^30 / d_model]
     uint32_t *status_hdev = nullptr;    // device-visible address of status_host
     std::vector<uint64_t> res_version;  // per layer: layer version uploaded
     std::vector<uint8_t> direct_ok;     // per layer: last forward needed no fill
@@ -752,6 +749,7 @@ msi_status msi_plan_create(const msi_plan_desc *desc, msi_plan **out)
         hipMalloc(&p->arrive_dev, 256) != hipSuccess ||
         hipMalloc(&p->dlist_dev, 4 * (E + 1) * sizeof(WorkItem)) != hipSuccess ||
         hipMalloc(&p->dcount_dev, 4 * sizeof(DevCount)) != hipSuccess ||
+        (desc->wdtype == MSI_W_KQ && hipMalloc(&p->xexp_dev, (size_t(1) << 30) / desc->d_model) != hipSuccess) ||
         hipMalloc(&p->table_dev, p->table_cap * sizeof(WorkItem)) != hipSuccess)
         return cleanup(MSI_E_DEVICE, "device allocation failed");
     if (hipHostMalloc(&p->table_host, p->table_cap * sizeof(WorkItem), hipHostMallocDefault) != hipSuccess ||
@@ -812,6 +810,8 @@ msi_status msi_plan_destroy(msi_plan *p)
         (void)hipFree(p->dlist_dev);
     if (p->dcount_dev)
         (void)hipFree(p->dcount_dev);
+    if (p->xexp_dev)
+        (void)hipFree(p->xexp_dev);
     if (p->res_host)
         (void)hipHostFree(p->res_host);
     if (p->tail_host)
@@ -1176,6 +1176,12 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
         X.d = D;
         X.I = I;
         ExpertLaunch GT = X, DT = X, GS = X, DS = X;
+        if (d.wdtype == MSI_W_KQ) {
+            HIP_OK(p->timed_launch(MSI_K_PERMUTE, cs,
+                                   [&] { return launch_kq_rows_f16(a->x, B.ys, p->xexp_dev, T, D, cs); }));
+            GT.xh = B.ys;
+            GT.xexp = p->xexp_dev;
+        }
         GT.items = W.items[0];
         GT.dev_n = p->dcount_dev + 0;
         GT.n_tiles = tile_ub(W.gu);
@@ -1273,9 +1279,13 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
     const bool has_shared = a->shared_object && T > 0;
     if (has_shared && sched.rounds.empty())
         launches.emplace_back();
+    // The shared expert rides in the first round's launches; in the quantized mix's last, because until its
+    // outputs are written their place (ys) holds the tile path's fp16 tokens.
+    const size_t shared_round = d.wdtype == MSI_W_KQ ? launches.size() - 1 : 0;
+    bool any_tile = false;
     for (size_t r = 0; r < launches.size(); ++r) {
         std::vector<WorkItem> tile_items, stream_items;
-        if (r == 0 && has_shared)   // the shared expert rides in the first round's launches
+        if (r == shared_round && has_shared)
             (f32 || uint32_t(T) > thr ? tile_items : stream_items).push_back(WorkItem{-1, -1, 0u, 0, T, 0});
         const std::vector<SchedItem> none;
         for (const SchedItem &si : r < sched.rounds.size() ? sched.rounds[r].items : none) {
@@ -1283,6 +1293,7 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
                        counts[si.expert], 0};
             (f32 || uint32_t(w.nrows) > thr ? tile_items : stream_items).push_back(w);
         }
+        any_tile |= !tile_items.empty();
         add_launch(r, GU_TILE, tile_items);
         add_launch(r, GU_STREAM, stream_items);      // (empty for f32 layers)
         add_launch(r, DN_TILE, tile_items);
@@ -1295,6 +1306,9 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
         HIP_OK(hipMemcpyAsync(p->table_dev, p->table_host, table.size() * sizeof(WorkItem), hipMemcpyHostToDevice,
                               cs));
     }
+    if (any_tile && d.wdtype == MSI_W_KQ)
+        HIP_OK(p->timed_launch(MSI_K_PERMUTE, cs,
+                               [&] { return launch_kq_rows_f16(a->x, B.ys, p->xexp_dev, T, D, cs); }));
     if (!p->status_clean)
         HIP_OK(launch_clear_word(p->status_dev, cs));
     p->status_clean = false;            // set again below once the word is read back as zero
@@ -1400,6 +1414,8 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
             L.shared_w = static_cast<const uint8_t *>(a->shared_object);
             L.act_s = B.act_s;
             L.ys = B.ys;
+            L.xh = B.ys;
+            L.xexp = p->xexp_dev;
             static const int tkind[NKIND] = {MSI_K_GATEUP_TILE, MSI_K_GATEUP_STREAM, MSI_K_DOWN_TILE,
                                              MSI_K_DOWN_STREAM};
             const hipError_t e = p->timed_launch(f32 ? MSI_K_EXPERT_F32 : tkind[l.kind], cs, [&] {

@@ -20,6 +20,7 @@ ROUTER = synth.Workload("router_forms", 39, synth.LayerShape(4100, 256, 1000, 4,
 
 
 def test_tile_forms():
+    import torch  # noqa: F401  (loads its HIP runtime before the library)
     import oracle
     import paper_2608_23805_amd as msi
     li = synth.layer_inputs(LAYER)
@@ -45,9 +46,10 @@ def test_tile_forms():
 
 
 def test_router_forms():
+    import torch
+    import torch  # noqa: F401  (loads its HIP runtime before the library)
     import oracle
     import paper_2608_23805_amd as msi
-    import torch
     li = synth.layer_inputs(ROUTER, lazy=True)
     dl = device_layer(li)
     s = ROUTER.shape
