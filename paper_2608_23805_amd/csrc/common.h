@@ -70,6 +70,28 @@ __device__ __forceinline__ bf16x8 as_bf16x8(const T &v)
     return __builtin_bit_cast(bf16x8, v);
 }
 
+// Eight bf16 elements 0 .. 7 of an MFMA fragment in the order 0 4 1 5 2 6 3 7:
+// the order in which masks and shifts alone take the 4-bit codes of a word
+// apart (codes 4 apart share a 16-bit lane pair).  A dot product does not
+// depend on the order as long as both operands have it.
+__device__ __forceinline__ bf16x8 pair_order(const u32x4 &v)
+{
+    const u32x4 r = {__builtin_amdgcn_perm(v[2], v[0], 0x05040100u), __builtin_amdgcn_perm(v[2], v[0], 0x07060302u),
+                     __builtin_amdgcn_perm(v[3], v[1], 0x05040100u), __builtin_amdgcn_perm(v[3], v[1], 0x07060302u)};
+    return __builtin_bit_cast(bf16x8, r);
+}
+
+// Eight unsigned 4-bit codes (element e at bits 4e) as exact bf16 128 + q (the
+// bits 0x4300 | q) in pair order: seven operations.
+__device__ __forceinline__ bf16x8 unpack_u4_pairs(uint32_t w)
+{
+    u32x4 r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        r[i] = ((w >> (4 * i)) & 0x000F000Fu) | 0x43004300u;
+    return __builtin_bit_cast(bf16x8, r);
+}
+
 // Work item of one expert inside a launch: rows [row0, row0 + nrows) of the
 // permuted order, weights at pool + slot * stride, expected generation gen.
 // slot < 0 marks the shared expert (weights given directly, no generation).
@@ -404,6 +426,7 @@ struct WaveRows {
         }
     }
     // write the rows to the wavefront's region (see below for why no wait follows)
+    template <bool HOLD = false>
     __device__ __forceinline__ void store(uint8_t *lds, int lane) const
     {
 #pragma unroll
@@ -412,6 +435,12 @@ struct WaveRows {
             if (row < 16)
                 *reinterpret_cast<u32x4 *>(lds + row * RS + 16 * ch) = v[k];
         }
+        // Other lanes wrote what this lane reads next.  Where not every lane stores, one that does not could keep an
+        // earlier chunk's word, as nothing it did itself changed it: there memory is opaque from here on.  HOLD asks
+        // for the same where it pays to have every load of the chunk issued before the first word is read back
+        // (int4: down 75 -> 66 us on a 1013-token batch; the quantized mix, short of registers: 88 -> 106).
+        if constexpr (HOLD || (16 * CPR) % 64 != 0)
+            asm volatile("" ::: "memory");
     }
 };
 

@@ -40,22 +40,6 @@ constexpr uint32_t BF16_ONE2 = 0x3F803F80u;        // two bf16 1.0
 __device__ __forceinline__ float h2f(uint16_t h) { return float(__builtin_bit_cast(_Float16, h)); }
 __device__ __forceinline__ uint16_t f16_bits(float f) { return __builtin_bit_cast(uint16_t, _Float16(f)); }
 
-// 8 unsigned nibbles (element e at bits 4e) -> 8 bf16 values 128 + q, exact
-// (bf16 numbers in [128, 256) are the integers: bits 0x4300 | q).  A partial
-// sum over these is the partial over q plus 128 times the sum of the other
-// operand, which the callers subtract with the sub-block's min term.
-__device__ __forceinline__ bf16x8 unpack_u4_128(uint32_t q)
-{
-    const uint32_t ev = q & 0x0F0F0F0Fu;               // elements 0, 2, 4, 6 in bytes 0..3
-    const uint32_t od = (q >> 4) & 0x0F0F0F0Fu;        // elements 1, 3, 5, 7
-    u32x4 r;
-    r[0] = (ev & 0xFFu) | ((od & 0xFFu) << 16) | 0x43004300u;
-    r[1] = ((ev >> 8) & 0xFFu) | ((od << 8) & 0xFF0000u) | 0x43004300u;
-    r[2] = ((ev >> 16) & 0xFFu) | (od & 0xFF0000u) | 0x43004300u;
-    r[3] = (ev >> 24) | ((od >> 8) & 0xFF0000u) | 0x43004300u;
-    return __builtin_bit_cast(bf16x8, r);
-}
-
 // 8 k6 elements: low nibbles (element e at bits 4e of lo) and 2-bit high
 // parts (element e at bits 2e of hi) -> 8 exact bf16 values q - 32.  The
 // codes are assembled one per byte (even and odd elements in two words), each
@@ -145,136 +129,138 @@ namespace kqs {
 constexpr int WAVES = 4, ROWS = 16;
 }
 
-int tiles_gateup_kq_stream(int nrows, int d, int I)
-{
-    (void)nrows;
-    (void)d;
-    return I / kqs::ROWS;
-}
-
-int tiles_down_kq_stream(int nrows, int d, int I)
-{
-    (void)nrows;
-    (void)I;
-    return d / (kqs::WAVES * kqs::ROWS);
-}
-
-// Gate/up, k4 stream path: a workgroup owns 16 rows of Wg and of Wu; its four
-// wavefronts take the quarters of d and add their partial sums in wavefront
-// order.  Tokens are the A operand and weights the B operand, so lane
-// (r = lane % 16, g = lane / 16) holds elements 8g .. 8g + 7 of each block of
-// token r and of weight row i0 + r, and its outputs are tokens 4g .. 4g + 3
-// of weight row i0 + r: one row's sub-block coefficients per lane.  Token
-// fragments come straight from global memory (the few rows of a decode step
-// stay in cache; lanes past the item's rows repeat its last row and are not
-// stored); weights go through WaveRows.  Blocks go in chunks of CH (CH
-// divides 8: at most one super-block), each chunk's loads issued before its
-// first MFMA.  The four lanes of a weight row share the decoding of its
-// sub-block coefficients: lane (r, g) decodes those of blocks g, g + 4 of
+// Gate/up, k4 stream path: a workgroup owns 16 R rows of Wg and of Wu; its
+// four wavefronts take the quarters of d and add their partial sums in
+// wavefront order.  Tokens are the A operand and weights the B operand, so
+// lane (r = lane % 16, g = lane / 16) holds elements 8g .. 8g + 7 of each block
+// of token r and of weight rows i0 + 16 m + r, and its outputs are tokens
+// 4g .. 4g + 3 of those rows: one row's sub-block coefficients per lane and
+// row group.  Token fragments come straight from global memory (the few rows
+// of a decode step stay in cache; lanes past the item's rows repeat its last
+// row and are not stored); weights go through WaveRows.  Blocks go in chunks
+// of CH (CH divides 8: at most one super-block), each chunk's loads issued
+// before its first MFMA.  The four lanes of a weight row share the decoding of
+// its sub-block coefficients: lane (r, g) decodes those of blocks g, g + 4 of
 // the chunk into the wavefront's LDS table, and every lane reads the block's
-// four coefficients back.  Chunks of 8 and the table keep the kernel at 80
-// registers, three workgroups per CU.
-template <int CH>
-__global__ void __launch_bounds__(256, 3) stream_gateup_kq_kernel(ExpertLaunch L)
+// coefficients back.  R = 2 where a launch has many items: a token fragment
+// (1 KiB from 16 rows) then serves twice the codes (see the 4-bit kernels).
+template <int CH, int R>
+__global__ void __launch_bounds__(256, R == 1 ? 3 : 2) stream_gateup_kq_kernel(ExpertLaunch L)
 {
     using Rows = WaveRows<16 * CH>;
-    __shared__ __attribute__((aligned(16))) uint8_t wst[kqs::WAVES][2][16 * Rows::RS];
-    // the coefficient table of the chunks, then the cross-wavefront sums (after a barrier)
-    __shared__ f32x4 cbuf[kqs::WAVES * CH * 16 > 3 * 2 * 64 ? kqs::WAVES * CH * 16 : 3 * 2 * 64];
-    f32x4 (*coef)[CH][16] = reinterpret_cast<f32x4 (*)[CH][16]>(cbuf);   // {a_g, b_g, a_u, b_u} of block u, row r
-    f32x4 (*red)[2][64] = reinterpret_cast<f32x4 (*)[2][64]>(cbuf);
+    constexpr int NM = 2 * R;                          // 16-row groups: R of Wg, then R of Wu
+    constexpr int REGION = NM * 16 * Rows::RS > NM * 1024 ? NM * 16 * Rows::RS : NM * 1024;
+    // a wavefront's rows, then (its own part) its partial sums
+    __shared__ __attribute__((aligned(16))) uint8_t wst[kqs::WAVES][REGION];
+    __shared__ float2 coef[kqs::WAVES][CH][NM][16];    // {a, b} of block u, row group m, row r
     int t;
     WorkItem it;
-    if (!kq_tile(L, L.I / kqs::ROWS, t, it) || it.nrows == 0 ||
+    if (!kq_tile(L, L.I / (kqs::ROWS * R), t, it) || it.nrows == 0 ||
         !slot_current(it, L.gen_dev, L.status))      // nrows 0: unpublished expert, no work
         return;
     static_assert(CH <= 8, "a chunk stays within one super-block");
     const int n = it.nrows, d = L.d, I = L.I, nsb = d / 256, nq = d / 32 / kqs::WAVES;
     const bool sh = it.slot < 0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i0 = (t - it.tile0) * kqs::ROWS;
+    const int i0 = (t - it.tile0) * kqs::ROWS * R;
     const int r = lane & 15, g = lane >> 4;
     const int bq = wave * nq;                          // this wavefront's first block
     const uint8_t *base = sh ? L.shared_w : L.wbase + uint64_t(it.slot) * L.wstride;
     const uint32_t mb = k4_bytes(I, d);
-    const uint8_t *qrows[2];
-    const u32x4 *hp[2];
+    const uint8_t *qrows[NM];
+    const u32x4 *hp[NM];
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const uint8_t *mat = base + m * mb;
-        qrows[m] = mat + int64_t(i0) * (d / 2) + 16 * bq;
-        hp[m] = reinterpret_cast<const u32x4 *>(mat + uint32_t(I) * uint32_t(d / 2)) + int64_t(i0 + r) * nsb;
+    for (int m = 0; m < NM; ++m) {
+        const uint8_t *mat = base + (m / R) * mb;
+        const int row = i0 + 16 * (m % R);
+        qrows[m] = mat + int64_t(row) * (d / 2) + 16 * bq;
+        hp[m] = reinterpret_cast<const u32x4 *>(mat + uint32_t(I) * uint32_t(d / 2)) + int64_t(row + r) * nsb;
     }
     const int tr = min(r, n - 1);
     const int64_t xrow = sh ? int64_t(it.row0 + tr) : int64_t(L.perm[it.row0 + tr]);
     const uint16_t *xp = reinterpret_cast<const uint16_t *>(L.x) + xrow * d + 8 * g + 32 * bq;
-    Rows wr[2];
-    u32x4 xv[CH], hd[2];                               // token fragments; the chunk's super-block headers
+    Rows wr[NM];
+    u32x4 xv[CH], hd[NM];                              // token fragments; the chunk's super-block headers
     auto issue = [&](int c0) {
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < NM; ++m)
             wr[m].load(qrows[m] + 16 * c0, d / 2, lane);
 #pragma unroll
         for (int u = 0; u < CH; ++u)
             xv[u] = *reinterpret_cast<const u32x4 *>(xp + 32 * (c0 + u));
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < NM; ++m)
             hd[m] = hp[m][(bq + c0) >> 3];
     };
     const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{BF16_ONE2, BF16_ONE2, BF16_ONE2, BF16_ONE2});
-    f32x4 ag = {0.f, 0.f, 0.f, 0.f}, au = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[NM];
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+        acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int c0 = 0; c0 < nq; c0 += CH) {
         issue(c0);
-        wr[0].store(wst[wave][0], lane);
-        wr[1].store(wst[wave][1], lane);
-        const uint8_t *q0 = wst[wave][0] + r * Rows::RS + 4 * g, *q1 = wst[wave][1] + r * Rows::RS + 4 * g;
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+            wr[m].store(wst[wave] + m * 16 * Rows::RS, lane);
+        const uint8_t *q = wst[wave] + r * Rows::RS + 4 * g;
 #pragma unroll
         for (int u0 = 0; u0 < CH; u0 += 4) {
             const int u = u0 + g;
             if (u < CH) {
                 const int j = (bq + c0 + u) & 7;       // sub-block within the super-block
-                float a_g, b_g, a_u, b_u;
-                k4_coef128(hd[0], j, a_g, b_g);
-                k4_coef128(hd[1], j, a_u, b_u);
-                coef[wave][u][r] = f32x4{a_g, b_g, a_u, b_u};
+#pragma unroll
+                for (int m = 0; m < NM; ++m) {
+                    float a, b;
+                    k4_coef128(hd[m], j, a, b);
+                    coef[wave][u][m][r] = make_float2(a, b);
+                }
             }
         }
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-            const bf16x8 xb = as_bf16x8(xv[u]);
-            const f32x4 pg = mfma16(xb, unpack_u4_128(*reinterpret_cast<const uint32_t *>(q0 + 16 * u)),
-                                    f32x4{0.f, 0.f, 0.f, 0.f});
-            const f32x4 pu = mfma16(xb, unpack_u4_128(*reinterpret_cast<const uint32_t *>(q1 + 16 * u)),
-                                    f32x4{0.f, 0.f, 0.f, 0.f});
+            const bf16x8 xb = pair_order(xv[u]);
             const f32x4 sx = mfma16(xb, ones, f32x4{0.f, 0.f, 0.f, 0.f});    // the tokens' sums over the block
-            const f32x4 cf = coef[wave][u][r];
-            const float a_g = cf[0], b_g = cf[1], a_u = cf[2], b_u = cf[3];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                ag[i] = fmaf(a_g, pg[i], ag[i]);
-                ag[i] = fmaf(-b_g, sx[i], ag[i]);
-                au[i] = fmaf(a_u, pu[i], au[i]);
-                au[i] = fmaf(-b_u, sx[i], au[i]);
+            for (int m = 0; m < NM; ++m) {
+                const f32x4 part =
+                    mfma16(xb, unpack_u4_pairs(*reinterpret_cast<const uint32_t *>(q + m * 16 * Rows::RS + 16 * u)),
+                           f32x4{0.f, 0.f, 0.f, 0.f});
+                const float2 cf = coef[wave][u][m][r];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    acc[m][i] = fmaf(cf.x, part[i], acc[m][i]);
+                    acc[m][i] = fmaf(-cf.y, sx[i], acc[m][i]);
+                }
             }
         }
     }
-    // quarters of d added in wavefront order
-    __syncthreads();                                   // (the table's last reads are done)
+    // quarters of d added in wavefront order (a wavefront's LDS operations execute in order, so its sums may take
+    // the place of its rows)
     if (wave > 0) {
-        red[wave - 1][0][lane] = ag;
-        red[wave - 1][1][lane] = au;
+        f32x4 *red = reinterpret_cast<f32x4 *>(wst[wave]);
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+            red[m * 64 + lane] = acc[m];
     }
     __syncthreads();
     if (wave != 0)
         return;
+#pragma unroll
+    for (int w = 1; w < kqs::WAVES; ++w)
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            const f32x4 v = reinterpret_cast<const f32x4 *>(wst[w])[m * 64 + lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc[m][i] += v[i];
+        }
     uint16_t *act = reinterpret_cast<uint16_t *>(sh ? L.act_s : L.act) + int64_t(it.row0) * I + i0 + r;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float gv = ((ag[i] + red[0][0][lane][i]) + red[1][0][lane][i]) + red[2][0][lane][i];
-        const float uv = ((au[i] + red[0][1][lane][i]) + red[1][1][lane][i]) + red[2][1][lane][i];
-        if (4 * g + i < n)
-            act[int64_t(4 * g + i) * I] = f32_to_bf16(silu(gv) * uv);
-    }
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int m = 0; m < R; ++m)
+            if (4 * g + i < n)
+                act[int64_t(4 * g + i) * I + 16 * m] = f32_to_bf16(silu(acc[m][i]) * acc[m + R][i]);
 }
 
 // Down, k6 stream path: a workgroup owns 64 output columns (16 per wavefront)
@@ -367,6 +353,20 @@ __global__ void __launch_bounds__(256, 2) stream_down_kq_kernel(ExpertLaunch L)
     }
 }
 
+namespace {
+
+template <int R>
+int tiles_gateup_kq_stream(int, int, int I)
+{
+    return I / (kqs::ROWS * R);
+}
+
+int tiles_down_kq_stream(int, int d, int)
+{
+    return d / (kqs::WAVES * kqs::ROWS);
+}
+
+template <int R>
 hipError_t launch_gateup_kq_stream(const ExpertLaunch &L, hipStream_t s)
 {
     if (L.n_tiles == 0)
@@ -376,11 +376,11 @@ hipError_t launch_gateup_kq_stream(const ExpertLaunch &L, hipStream_t s)
     // chunk: 8, 4 or 2 blocks, dividing a quarter of d's blocks (d / 128)
     const int nq = L.d / 128;
     if (nq % 8 == 0)
-        launch_k(stream_gateup_kq_kernel<8>, L.n_tiles, 256, 0, s, L);
+        launch_k(stream_gateup_kq_kernel<8, R>, L.n_tiles, 256, 0, s, L);
     else if (nq % 4 == 0)
-        launch_k(stream_gateup_kq_kernel<4>, L.n_tiles, 256, 0, s, L);
+        launch_k(stream_gateup_kq_kernel<4, R>, L.n_tiles, 256, 0, s, L);
     else
-        launch_k(stream_gateup_kq_kernel<2>, L.n_tiles, 256, 0, s, L);
+        launch_k(stream_gateup_kq_kernel<2, R>, L.n_tiles, 256, 0, s, L);
     return hipGetLastError();
 }
 
@@ -396,6 +396,8 @@ hipError_t launch_down_kq_stream(const ExpertLaunch &L, hipStream_t s)
         launch_k(stream_down_kq_kernel<1>, L.n_tiles, 256, 0, s, L);
     return hipGetLastError();
 }
+
+}  // namespace
 
 // ============================================================== tile path
 //
@@ -924,10 +926,10 @@ using KqSmall = kqt::Shape<GU, 64, 128, 4, 3>;
 template <bool GU>
 using KqBig = kqt::Shape<GU, 128, 256, 4, 2>;
 
-template <template <bool> class S>
-const KernelSet kq_set{kq_tiles<S<true>>, tiles_gateup_kq_stream, kq_tiles<S<false>>, tiles_down_kq_stream,
+template <template <bool> class S, int R>
+const KernelSet kq_set{kq_tiles<S<true>>, tiles_gateup_kq_stream<R>, kq_tiles<S<false>>, tiles_down_kq_stream,
                        kq_geom<S<true>>, kq_geom<S<false>>,
-                       launch_kq_tile<S<true>>, launch_gateup_kq_stream,
+                       launch_kq_tile<S<true>>, launch_gateup_kq_stream<R>,
                        launch_kq_tile<S<false>>, launch_down_kq_stream};
 
 }  // namespace
@@ -942,7 +944,11 @@ const KernelSet kq_set{kq_tiles<S<true>>, tiles_gateup_kq_stream, kq_tiles<S<fal
 //     640      2431+1917  1906+1534      4134+3573
 const KernelSet &kq_kernels(uint64_t rows, uint64_t E)
 {
-    return rows <= 64 * E ? kq_set<KqSmall> : kq_set<KqBig>;
+    // (R of the stream gate/up by the routed rows, as for the 4-bit kernels; R = 1, R = 2, us: T 1 9.0, 10.8;
+    // T 4 18.0, 15.1; T 16 33.4, 30.5; T 251 116, 100)
+    if (rows < 32)
+        return kq_set<KqSmall, 1>;
+    return rows <= 64 * E ? kq_set<KqSmall, 2> : kq_set<KqBig, 2>;
 }
 
 hipError_t init_kq_attributes()

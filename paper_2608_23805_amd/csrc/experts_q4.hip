@@ -8,8 +8,9 @@
 //
 //  * stream path (<= 16 tokens per expert): tokens as the A operand and
 //    weights as the B operand, tokens read straight from memory and the
-//    nibbles through row-contiguous loads rearranged in LDS (WaveRows); the
-//    codes unpacked to exact bf16 q (C = 0).
+//    nibbles through row-contiguous loads rearranged in LDS (WaveRows); both
+//    operands in pair order (common.h), the codes as the exact bf16 136 + q,
+//    whose offset leaves through the C input as on the tile path.
 //  * tile path: 128 tokens x 128 weight rows per workgroup; A rows, packed
 //    nibbles and scales copied from memory straight into two LDS stage
 //    buffers (three workgroups per CU); the codes enter the MFMA as the exact
@@ -25,19 +26,6 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 __device__ __forceinline__ uint32_t q4_matrix_bytes(int rows, int cols)
 {
     return uint32_t(rows) * uint32_t(cols / 2) + uint32_t(rows) * uint32_t(cols / 32) * 2u;
-}
-
-// 8 nibbles (element e at bits 4e..4e+3) -> 8 exact bf16 values
-__device__ __forceinline__ bf16x8 unpack_q4(uint32_t q)
-{
-    u32x4 r;
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-        const int lo = int(q << (28 - 8 * h)) >> 28;          // element 2h
-        const int hi = int(q << (24 - 8 * h)) >> 28;          // element 2h + 1
-        r[h] = (__float_as_uint(float(lo)) >> 16) | (__float_as_uint(float(hi)) & 0xFFFF0000u);
-    }
-    return __builtin_bit_cast(bf16x8, r);
 }
 
 // 8 nibbles (element e at bits 4e..4e+3, two's complement q) -> 8 exact bf16
@@ -67,20 +55,6 @@ namespace q4s {
 constexpr int WAVES = 4, ROWS = 16;
 }
 
-int tiles_gateup_q4_stream(int nrows, int d, int I)
-{
-    (void)nrows;
-    (void)d;
-    return I / q4s::ROWS;
-}
-
-int tiles_down_q4_stream(int nrows, int d, int I)
-{
-    (void)nrows;
-    (void)I;
-    return d / (q4s::WAVES * q4s::ROWS);
-}
-
 // Tile t of a stream launch and its item: from the device-built list (the
 // grid is then an upper bound) or the host list.
 __device__ __forceinline__ bool q4_tile(const ExpertLaunch &L, int per_item, int &t, WorkItem &it)
@@ -105,14 +79,7 @@ __device__ __forceinline__ bool q4_tile(const ExpertLaunch &L, int per_item, int
 template <int CH>
 __device__ __forceinline__ void load_scales(uint32_t (&w)[CH / 2], const uint16_t *p)
 {
-    if constexpr (CH == 16) {
-        const u32x4 a = reinterpret_cast<const u32x4 *>(p)[0], b = reinterpret_cast<const u32x4 *>(p)[1];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            w[i] = a[i];
-            w[4 + i] = b[i];
-        }
-    } else if constexpr (CH == 8) {
+    if constexpr (CH == 8) {
         const u32x4 a = *reinterpret_cast<const u32x4 *>(p);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -131,23 +98,28 @@ __device__ __forceinline__ float scale_at(const uint32_t *w, int b)
     return half_to_float(uint16_t(w[b >> 1] >> (16 * (b & 1))));
 }
 
-// Gate/up, 4-bit stream path: a workgroup owns 16 rows of Wg and of Wu; its
+// Gate/up, 4-bit stream path: a workgroup owns 16 R rows of Wg and of Wu; its
 // four wavefronts take the four quarters of d and add their fp32 partial sums
-// in wavefront order before SiLU(g) * u, so an item is I / 16 workgroups.
+// in wavefront order before SiLU(g) * u, so an item is I / (16 R) workgroups.
 // Tokens are the A operand and weights the B operand: lane (r = lane % 16,
 // g = lane / 16) holds elements 8g .. 8g + 7 of each block of token r and of
-// weight row i0 + r, and its outputs are tokens 4g .. 4g + 3 of that weight
-// row, so each lane applies one row's block scales.  Token fragments come
+// weight rows i0 + 16 q + r, and its outputs are tokens 4g .. 4g + 3 of those
+// rows, so each lane applies its rows' block scales.  Token fragments come
 // straight from global memory (lanes past the item's rows repeat its last
 // row and are not stored); the nibbles go through WaveRows (row-contiguous
 // 16-byte loads, rearranged in the wavefront's own LDS region).  Blocks go
-// in chunks of CH, each chunk's loads issued before its first MFMA.
-template <int CH>
+// in chunks of CH, each chunk's loads issued before its first MFMA.  A token
+// fragment is 1 KiB from 16 rows and R = 1 gives it to 512 bytes of codes: the
+// fragment loads, not the codes or the arithmetic, bound the kernel (halving
+// its vector operations alone gained 5%), so launches of many items take R = 2.
+template <int CH, int R>
 __global__ void __launch_bounds__(256, 2) stream_gateup_q4_kernel(ExpertLaunch L)
 {
     using Rows = WaveRows<16 * CH>;
-    __shared__ __attribute__((aligned(16))) uint8_t wst[q4s::WAVES][2][16 * Rows::RS];
-    __shared__ f32x4 red[3][2][64];
+    constexpr int NM = 2 * R;                          // 16-row groups: R of Wg, then R of Wu
+    constexpr int REGION = NM * 16 * Rows::RS > NM * 1024 ? NM * 16 * Rows::RS : NM * 1024;
+    // a wavefront's rows, then (its own part) its partial sums
+    __shared__ __attribute__((aligned(16))) uint8_t wst[q4s::WAVES][REGION];
     const int d = L.d, I = L.I, nblk = d / 32, nq = nblk / q4s::WAVES;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
@@ -164,30 +136,31 @@ __global__ void __launch_bounds__(256, 2) stream_gateup_q4_kernel(ExpertLaunch L
     }
     int t;
     WorkItem it;
-    if (!q4_tile(L, L.I / q4s::ROWS, t, it) || it.nrows == 0)   // nrows 0: unpublished expert, no work
+    if (!q4_tile(L, I / (q4s::ROWS * R), t, it) || it.nrows == 0)   // nrows 0: unpublished expert, no work
         return;
     const uint32_t gnow = slot_gen_now(it, L.gen_dev);
     const int n = it.nrows;
     const bool sh = it.slot < 0;
-    const int i0 = (t - it.tile0) * q4s::ROWS;
+    const int i0 = (t - it.tile0) * q4s::ROWS * R;
     const uint8_t *base = sh ? L.shared_w : L.wbase + uint64_t(it.slot) * L.wstride;
     const uint32_t mb = q4_matrix_bytes(I, d);
-    const uint8_t *qrows[2];
-    const uint16_t *sp[2];
+    const uint8_t *qrows[NM];
+    const uint16_t *sp[NM];
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const uint8_t *mat = base + m * mb;
-        qrows[m] = mat + int64_t(i0) * (d / 2) + 16 * bq;
-        sp[m] = reinterpret_cast<const uint16_t *>(mat + int64_t(I) * (d / 2)) + int64_t(i0 + r) * nblk + bq;
+    for (int m = 0; m < NM; ++m) {
+        const uint8_t *mat = base + (m / R) * mb;
+        const int row = i0 + 16 * (m % R);
+        qrows[m] = mat + int64_t(row) * (d / 2) + 16 * bq;
+        sp[m] = reinterpret_cast<const uint16_t *>(mat + int64_t(I) * (d / 2)) + int64_t(row + r) * nblk + bq;
     }
     const int tr = min(r, n - 1);
     const int64_t xrow = one ? 0 : sh ? int64_t(it.row0 + tr) : int64_t(L.perm[it.row0 + tr]);
     const uint16_t *xp = reinterpret_cast<const uint16_t *>(L.x) + xrow * d + 8 * g + 32 * bq;
-    Rows wr[2];
-    uint32_t sc[2][CH / 2];
+    Rows wr[NM];
+    uint32_t sc[NM][CH / 2];
     auto issue = [&](int c0) {
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < NM; ++m)
             wr[m].load(qrows[m] + 16 * c0, d / 2, lane);
         if (!(one && c0 == 0)) {
 #pragma unroll
@@ -195,62 +168,78 @@ __global__ void __launch_bounds__(256, 2) stream_gateup_q4_kernel(ExpertLaunch L
                 xv[u] = *reinterpret_cast<const u32x4 *>(xp + 32 * (c0 + u));
         }
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < NM; ++m)
             load_scales<CH>(sc[m], sp[m] + c0);
     };
-    f32x4 ag = {0.f, 0.f, 0.f, 0.f}, au = {0.f, 0.f, 0.f, 0.f};
+    const bf16x8 neg136 = __builtin_bit_cast(bf16x8, u32x4{0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u});
+    f32x4 acc[NM];
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+        acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int c0 = 0; c0 < nq; c0 += CH) {
         issue(c0);
-        wr[0].store(wst[wave][0], lane);
-        wr[1].store(wst[wave][1], lane);
-        const uint8_t *q0 = wst[wave][0] + r * Rows::RS + 4 * g, *q1 = wst[wave][1] + r * Rows::RS + 4 * g;
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+            wr[m].template store<true>(wst[wave] + m * 16 * Rows::RS, lane);
+        const uint8_t *q = wst[wave] + r * Rows::RS + 4 * g;
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-            const bf16x8 xb = as_bf16x8(xv[u]);
-            const f32x4 pg = mfma16(xb, unpack_q4(*reinterpret_cast<const uint32_t *>(q0 + 16 * u)),
-                                    f32x4{0.f, 0.f, 0.f, 0.f});
-            const f32x4 pu = mfma16(xb, unpack_q4(*reinterpret_cast<const uint32_t *>(q1 + 16 * u)),
-                                    f32x4{0.f, 0.f, 0.f, 0.f});
-            const float s_g = scale_at(sc[0], u), s_u = scale_at(sc[1], u);
+            const bf16x8 xb = pair_order(xv[u]);
+            const f32x4 corr = mfma16(xb, neg136, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                ag[k] = fmaf(s_g, pg[k], ag[k]);
-                au[k] = fmaf(s_u, pu[k], au[k]);
+            for (int m = 0; m < NM; ++m) {
+                const uint32_t w = *reinterpret_cast<const uint32_t *>(q + m * 16 * Rows::RS + 16 * u);
+                const f32x4 part = mfma16(xb, unpack_u4_pairs(w ^ 0x88888888u), corr);
+                const float s = scale_at(sc[m], u);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    acc[m][k] = fmaf(s, part[k], acc[m][k]);
             }
         }
     }
-    // quarters of d added in wavefront order
+    // quarters of d added in wavefront order (a wavefront's LDS operations execute in order, so its sums may take
+    // the place of its rows)
+    f32x4 *red = reinterpret_cast<f32x4 *>(wst[wave]);
     if (wave > 0) {
-        red[wave - 1][0][lane] = ag;
-        red[wave - 1][1][lane] = au;
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+            red[m * 64 + lane] = acc[m];
     }
     __syncthreads();
     if (wave != 0 || !slot_gen_ok(it, gnow, L.status))
         return;
+#pragma unroll
+    for (int w = 1; w < q4s::WAVES; ++w)
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            const f32x4 v = reinterpret_cast<const f32x4 *>(wst[w])[m * 64 + lane];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                acc[m][k] += v[k];
+        }
     uint16_t *act = reinterpret_cast<uint16_t *>(sh ? L.act_s : L.act) + int64_t(it.row0) * I + i0 + r;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float gv = ((ag[k] + red[0][0][lane][k]) + red[1][0][lane][k]) + red[2][0][lane][k];
-        const float uv = ((au[k] + red[0][1][lane][k]) + red[1][1][lane][k]) + red[2][1][lane][k];
-        if (4 * g + k < n)
-            act[int64_t(4 * g + k) * I] = f32_to_bf16(silu(gv) * uv);
-    }
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int m = 0; m < R; ++m)
+            if (4 * g + k < n)
+                act[int64_t(4 * g + k) * I + 16 * m] = f32_to_bf16(silu(acc[m][k]) * acc[m + R][k]);
 }
 
-// Down, 4-bit stream path: a workgroup owns 64 output columns (16 per
+// Down, 4-bit stream path: a workgroup owns 64 R output columns (16 R per
 // wavefront) over all of I, in chunks of CH blocks whose nibbles (through
 // WaveRows), act fragments and this lane's block scales are issued together.
 // Act rows are the A operand, read straight from global memory (lanes past
 // the item's rows repeat its last row), and weights the B operand (outputs:
-// tokens 4g .. 4g + 3 of column c0 + r).
-template <int CH>
+// tokens 4g .. 4g + 3 of columns c0 + 16 m + r).
+template <int CH, int R>
 __global__ void __launch_bounds__(256, 2) stream_down_q4_kernel(ExpertLaunch L)
 {
     using Rows = WaveRows<16 * CH>;
-    __shared__ __attribute__((aligned(16))) uint8_t wst[q4s::WAVES][16 * Rows::RS];
+    __shared__ __attribute__((aligned(16))) uint8_t wst[q4s::WAVES][R * 16 * Rows::RS];
     int t;
     WorkItem it;
-    if (!q4_tile(L, L.d / (q4s::WAVES * q4s::ROWS), t, it) || it.nrows == 0)   // nrows 0: unpublished expert
+    if (!q4_tile(L, L.d / (q4s::WAVES * q4s::ROWS * R), t, it) || it.nrows == 0)   // nrows 0: unpublished expert
         return;
     // the generation is read here and compared before the stores, and the row weights are read with the
     // first weights, so nothing waits between the item lookup and the weight loads
@@ -258,7 +247,7 @@ __global__ void __launch_bounds__(256, 2) stream_down_q4_kernel(ExpertLaunch L)
     const int n = it.nrows, d = L.d, I = L.I, nblk = I / 32;
     const bool sh = it.slot < 0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c0 = ((t - it.tile0) * q4s::WAVES + wave) * q4s::ROWS;
+    const int c0 = ((t - it.tile0) * q4s::WAVES + wave) * q4s::ROWS * R;
     const int r = lane & 15, g = lane >> 4;
     const uint8_t *base = sh ? L.shared_w : L.wbase + uint64_t(it.slot) * L.wstride;
     const uint8_t *wd = base + 2 * q4_matrix_bytes(I, d);
@@ -266,30 +255,45 @@ __global__ void __launch_bounds__(256, 2) stream_down_q4_kernel(ExpertLaunch L)
     const uint16_t *sp = reinterpret_cast<const uint16_t *>(wd + int64_t(d) * (I / 2)) + int64_t(c0 + r) * nblk;
     const uint16_t *ap = reinterpret_cast<const uint16_t *>(sh ? L.act_s : L.act) +
                          int64_t(it.row0 + min(r, n - 1)) * I + 8 * g;
-    Rows wr;
+    Rows wr[R];
     u32x4 av[CH];
-    uint32_t sc[CH / 2];
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    uint32_t sc[R][CH / 2];
+    const bf16x8 neg136 = __builtin_bit_cast(bf16x8, u32x4{0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u});
+    f32x4 acc[R];
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+        acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
     float rw[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
         rw[k] = (sh || 4 * g + k >= n) ? 1.0f : L.row_weight[it.row0 + 4 * g + k];
     for (int b0 = 0; b0 < nblk; b0 += CH) {
-        wr.load(qrows + 16 * b0, I / 2, lane);
+#pragma unroll
+        for (int m = 0; m < R; ++m)
+            wr[m].load(qrows + int64_t(16 * m) * (I / 2) + 16 * b0, I / 2, lane);
 #pragma unroll
         for (int u = 0; u < CH; ++u)
             av[u] = *reinterpret_cast<const u32x4 *>(ap + 32 * (b0 + u));
-        load_scales<CH>(sc, sp + b0);
-        wr.store(wst[wave], lane);
+#pragma unroll
+        for (int m = 0; m < R; ++m)
+            load_scales<CH>(sc[m], sp + int64_t(16 * m) * nblk + b0);
+#pragma unroll
+        for (int m = 0; m < R; ++m)
+            wr[m].template store<true>(wst[wave] + m * 16 * Rows::RS, lane);
         const uint8_t *q = wst[wave] + r * Rows::RS + 4 * g;
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-            const f32x4 part = mfma16(as_bf16x8(av[u]), unpack_q4(*reinterpret_cast<const uint32_t *>(q + 16 * u)),
-                                      f32x4{0.f, 0.f, 0.f, 0.f});
-            const float sv = scale_at(sc, u);
+            const bf16x8 ab = pair_order(av[u]);
+            const f32x4 corr = mfma16(ab, neg136, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                acc[k] = fmaf(sv, part[k], acc[k]);
+            for (int m = 0; m < R; ++m) {
+                const uint32_t w = *reinterpret_cast<const uint32_t *>(q + m * 16 * Rows::RS + 16 * u);
+                const f32x4 part = mfma16(ab, unpack_u4_pairs(w ^ 0x88888888u), corr);
+                const float sv = scale_at(sc[m], u);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    acc[m][k] = fmaf(sv, part[k], acc[m][k]);
+            }
         }
     }
     if (!slot_gen_ok(it, gnow, L.status))
@@ -297,39 +301,50 @@ __global__ void __launch_bounds__(256, 2) stream_down_q4_kernel(ExpertLaunch L)
     uint16_t *y = static_cast<uint16_t *>(sh ? L.ys : L.y) + int64_t(it.row0) * d + c0 + r;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        if (4 * g + k < n)
-            y[int64_t(4 * g + k) * d] = f32_to_bf16(acc[k] * rw[k]);
+#pragma unroll
+        for (int m = 0; m < R; ++m)
+            if (4 * g + k < n)
+                y[int64_t(4 * g + k) * d + 16 * m] = f32_to_bf16(acc[m][k] * rw[k]);
 }
 
-hipError_t launch_gateup_q4_stream(const ExpertLaunch &L, hipStream_t s)
+template <int R>
+static int tiles_gateup_q4_stream(int, int, int I)
+{
+    return I / (q4s::ROWS * R);
+}
+
+template <int R>
+static int tiles_down_q4_stream(int, int d, int)
+{
+    return d / (q4s::WAVES * q4s::ROWS * R);
+}
+
+template <int R>
+static hipError_t launch_gateup_q4_stream(const ExpertLaunch &L, hipStream_t s)
 {
     if (L.n_tiles == 0)
         return hipSuccess;
-    // chunk: the largest of 16, 8, 4, 2 blocks dividing a quarter of d (d % 256 == 0)
+    // chunk: the largest of 8, 4, 2 blocks dividing a quarter of d (d % 256 == 0)
     const int nq = L.d / 128;
-    if (nq % 16 == 0)
-        launch_k(stream_gateup_q4_kernel<16>, L.n_tiles, 256, 0, s, L);
-    else if (nq % 8 == 0)
-        launch_k(stream_gateup_q4_kernel<8>, L.n_tiles, 256, 0, s, L);
+    if (nq % 8 == 0)
+        launch_k(stream_gateup_q4_kernel<8, R>, L.n_tiles, 256, 0, s, L);
     else if (nq % 4 == 0)
-        launch_k(stream_gateup_q4_kernel<4>, L.n_tiles, 256, 0, s, L);
+        launch_k(stream_gateup_q4_kernel<4, R>, L.n_tiles, 256, 0, s, L);
     else
-        launch_k(stream_gateup_q4_kernel<2>, L.n_tiles, 256, 0, s, L);
+        launch_k(stream_gateup_q4_kernel<2, R>, L.n_tiles, 256, 0, s, L);
     return hipGetLastError();
 }
 
-hipError_t launch_down_q4_stream(const ExpertLaunch &L, hipStream_t s)
+template <int R>
+static hipError_t launch_down_q4_stream(const ExpertLaunch &L, hipStream_t s)
 {
     if (L.n_tiles == 0)
         return hipSuccess;
-    // chunk: the largest of 16, 8, 4 blocks dividing I / 32 (I % 128 == 0)
-    const int nblk = L.I / 32;
-    if (nblk % 16 == 0)
-        launch_k(stream_down_q4_kernel<16>, L.n_tiles, 256, 0, s, L);
-    else if (nblk % 8 == 0)
-        launch_k(stream_down_q4_kernel<8>, L.n_tiles, 256, 0, s, L);
+    // chunk: 8 or 4 blocks dividing I / 32 (I % 128 == 0)
+    if (L.I % 256 == 0)
+        launch_k(stream_down_q4_kernel<8, R>, L.n_tiles, 256, 0, s, L);
     else
-        launch_k(stream_down_q4_kernel<4>, L.n_tiles, 256, 0, s, L);
+        launch_k(stream_down_q4_kernel<4, R>, L.n_tiles, 256, 0, s, L);
     return hipGetLastError();
 }
 
@@ -347,25 +362,25 @@ constexpr int COPIES = 6;                   // copy instructions per wavefront p
 constexpr size_t LDS_BYTES = size_t(NBUF) * STAGE;
 }  // namespace q4t
 
-int tiles_gateup_q4_tile(int nrows, int d, int I)
+static int tiles_gateup_q4_tile(int nrows, int d, int I)
 {
     (void)d;
     return ((nrows + q4t::BM - 1) / q4t::BM) * (I / 64);
 }
 
-int tiles_down_q4_tile(int nrows, int d, int I)
+static int tiles_down_q4_tile(int nrows, int d, int I)
 {
     (void)I;
     return ((nrows + q4t::BM - 1) / q4t::BM) * (d / q4t::BN);
 }
 
-TileGeom geom_gateup_q4_tile(int d, int I)
+static TileGeom geom_gateup_q4_tile(int d, int I)
 {
     (void)d;
     return TileGeom{q4t::BM, I / 64};
 }
 
-TileGeom geom_down_q4_tile(int d, int I)
+static TileGeom geom_down_q4_tile(int d, int I)
 {
     (void)I;
     return TileGeom{q4t::BM, d / q4t::BN};
@@ -582,7 +597,7 @@ __global__ void __launch_bounds__(q4t::THREADS, 3) tile_q4_kernel(ExpertLaunch L
     }
 }
 
-hipError_t launch_gateup_q4_tile(const ExpertLaunch &L, hipStream_t s)
+static hipError_t launch_gateup_q4_tile(const ExpertLaunch &L, hipStream_t s)
 {
     if (L.n_tiles == 0)
         return hipSuccess;
@@ -590,12 +605,29 @@ hipError_t launch_gateup_q4_tile(const ExpertLaunch &L, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_down_q4_tile(const ExpertLaunch &L, hipStream_t s)
+static hipError_t launch_down_q4_tile(const ExpertLaunch &L, hipStream_t s)
 {
     if (L.n_tiles == 0)
         return hipSuccess;
     launch_k(tile_q4_kernel<false>, L.n_tiles, q4t::THREADS, q4t::LDS_BYTES, s, L);
     return hipGetLastError();
+}
+
+template <int R>
+static const KernelSet q4_set{tiles_gateup_q4_tile, tiles_gateup_q4_stream<R>, tiles_down_q4_tile,
+                              tiles_down_q4_stream<R>, geom_gateup_q4_tile, geom_down_q4_tile,
+                              launch_gateup_q4_tile, launch_gateup_q4_stream<R>, launch_down_q4_tile,
+                              launch_down_q4_stream<R>};
+
+// R of the stream kernels by the routed rows, which bound the launch's items:
+// from 32 on its workgroups fill the chip with R = 2 as well.  The two are
+// bit-identical.  Measured (MI355X, d 2048, I 512, K 10; gate/up + down, us,
+// R = 1, R = 2; in parentheses codes converted one by one, R = 1): T 1 6.8+5.2,
+// 9.1+6.1 (8.3+5.5); T 4 13.5+9.5, 13.6+9.1 (16.7+9.3); T 16 39.7+25.3,
+// 37.6+21.6 (48.2+29.1); T 1013 129+82, 116+66 (148+91).
+const KernelSet &q4_kernels(uint64_t rows, uint64_t)
+{
+    return rows >= 32 ? q4_set<2> : q4_set<1>;
 }
 
 hipError_t init_q4_attributes()

@@ -143,8 +143,6 @@ struct TileGeom {
 };
 TileGeom geom_gateup_tile(int d, int I);
 TileGeom geom_down_tile(int d, int I);
-TileGeom geom_gateup_q4_tile(int d, int I);
-TileGeom geom_down_q4_tile(int d, int I);
 
 // Device-built work list of a forward whose demanded experts are all
 // published (build_worklist_kernel): the four launch lists (tile and stream
@@ -180,21 +178,9 @@ hipError_t launch_gateup_f32(const ExpertLaunch &L, hipStream_t s);
 hipError_t launch_down_f32(const ExpertLaunch &L, hipStream_t s);
 
 // 4-bit block-quantized experts (experts_q4.hip)
-int tiles_gateup_q4_stream(int nrows, int d, int I);
-int tiles_down_q4_stream(int nrows, int d, int I);
-int tiles_gateup_q4_tile(int nrows, int d, int I);
-int tiles_down_q4_tile(int nrows, int d, int I);
-hipError_t launch_gateup_q4_stream(const ExpertLaunch &L, hipStream_t s);
-hipError_t launch_down_q4_stream(const ExpertLaunch &L, hipStream_t s);
-hipError_t launch_gateup_q4_tile(const ExpertLaunch &L, hipStream_t s);
-hipError_t launch_down_q4_tile(const ExpertLaunch &L, hipStream_t s);
 hipError_t init_q4_attributes();
 
 // quantized-expert mix, Wg / Wu in k4 and Wd in k6 (experts_kq.hip)
-int tiles_gateup_kq_stream(int nrows, int d, int I);
-int tiles_down_kq_stream(int nrows, int d, int I);
-hipError_t launch_gateup_kq_stream(const ExpertLaunch &L, hipStream_t s);
-hipError_t launch_down_kq_stream(const ExpertLaunch &L, hipStream_t s);
 // xh[t] = fp16(2^xexp[t] x[t]) in the k4 tiles' element order
 hipError_t launch_kq_rows_f16(const void *x, void *xh, int8_t *xexp, int T, int d, hipStream_t s);
 hipError_t init_kq_attributes();
@@ -212,6 +198,8 @@ struct KernelSet {
     Launch gu_tile, gu_stream, dn_tile, dn_stream;
 };
 // kernels of a batch of `rows` routed rows (T * K) over E experts
+const KernelSet &q4_kernels(uint64_t rows, uint64_t E);
+const KernelSet &q4_kernels(uint64_t rows, uint64_t E);
 const KernelSet &kq_kernels(uint64_t rows, uint64_t E);
 const KernelSet &bf16_kernels(uint64_t rows, uint64_t E);
 

@@ -66,13 +66,9 @@ const KernelSet &kernel_set(uint32_t wdtype, uint64_t rows, uint64_t E)
 {
     static const KernelSet f32{tiles_gateup_f32, nullptr, tiles_down_f32, nullptr, nullptr, nullptr,
                                launch_gateup_f32, nullptr, launch_down_f32, nullptr};
-    static const KernelSet q4{tiles_gateup_q4_tile, tiles_gateup_q4_stream, tiles_down_q4_tile,
-                              tiles_down_q4_stream, geom_gateup_q4_tile, geom_down_q4_tile,
-                              launch_gateup_q4_tile, launch_gateup_q4_stream, launch_down_q4_tile,
-                              launch_down_q4_stream};
     switch (wdtype) {
     case MSI_W_F32: return f32;
-    case MSI_W_Q4B32: return q4;
+    case MSI_W_Q4B32: return q4_kernels(rows, E);
     case MSI_W_KQ: return kq_kernels(rows, E);
     default: return bf16_kernels(rows, E);
     }
