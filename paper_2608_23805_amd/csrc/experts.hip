@@ -6,13 +6,15 @@
 //    MFMA A operand read straight from HBM in the 16x16x32 fragment layout
 //    (each wavefront owns 16 weight rows; each weight byte is read once), the
 //    expert's tokens (at most 16, zero-padded) are the B operand held in LDS.
-//  * f32 path (fp32 layers): FMA dot products in fixed sequential order.
+//  * f32 path (fp32 layers): FMA dot products in fixed sequential order
+//    (dot_f32.h).
 //
 // Every workgroup checks the slot generation first and writes nothing on a
 // mismatch (fail closed).  Outputs: act[row, I] = silu(x Wg^T) * (x Wu^T) and
 // y[row, d] = row_weight * (act Wd^T), rows in permuted order, both rounded
 // to bf16 once (fp32 throughout for fp32 layers).
 #include "common.h"
+#include "dot_f32.h"
 #include "kernels.h"
 
 namespace msi {
@@ -351,72 +353,85 @@ hipError_t launch_down_stream(const ExpertLaunch &L, hipStream_t s)
 
 // ============================================================== f32 path
 
-namespace f32p {
-constexpr int TR = 16, TC = 16;   // 16 rows x 16 columns per 256-thread block
-}
-
 int tiles_gateup_f32(int nrows, int d, int I)
 {
     (void)d;
-    return ((nrows + f32p::TR - 1) / f32p::TR) * (I / f32p::TC);
+    return ((nrows + f32t::ROWS - 1) / f32t::ROWS) * (I / f32t::COLS);
 }
 
 int tiles_down_f32(int nrows, int d, int I)
 {
     (void)I;
-    return ((nrows + f32p::TR - 1) / f32p::TR) * (d / f32p::TC);
+    return ((nrows + f32t::ROWS - 1) / f32t::ROWS) * (d / f32t::COLS);
+}
+
+TileGeom geom_gateup_f32(int d, int I)
+{
+    (void)d;
+    return TileGeom{f32t::ROWS, I / f32t::COLS};
+}
+
+TileGeom geom_down_f32(int d, int I)
+{
+    (void)I;
+    return TileGeom{f32t::ROWS, d / f32t::COLS};
 }
 
 __global__ void __launch_bounds__(256) gateup_f32_kernel(ExpertLaunch L)
 {
-    const int t = int(blockIdx.x);
-    const WorkItem it = L.items[find_item(L.items, L.n_items, t)];
+    __shared__ f32t::Stage<2> lds;
+    int n_items, n_tiles;
+    const int t = launch_tile(L, n_items, n_tiles);
+    if (t < 0)
+        return;                                   // past the device-built list's tiles
+    const WorkItem it = L.items[find_item(L.items, n_items, t)];
     if (!slot_current(it, L.gen_dev, L.status))
         return;
-    const int local = t - it.tile0;
-    const int nct = L.I / f32p::TC;
-    const int r = (local / nct) * f32p::TR + int(threadIdx.x) / f32p::TC;
-    const int c = (local % nct) * f32p::TC + int(threadIdx.x) % f32p::TC;
-    if (r >= it.nrows)
-        return;
-    const int d = L.d;
+    const int d = L.d, I = L.I;
+    const int local = t - it.tile0, nct = I / f32t::COLS;
+    const int m0 = (local / nct) * f32t::ROWS, c0 = (local % nct) * f32t::COLS;
     const bool sh = it.slot < 0;
-    const int64_t src = sh ? int64_t(it.row0 + r) : int64_t(L.perm[it.row0 + r]);
-    const float *x = reinterpret_cast<const float *>(L.x) + src * d;
     const uint8_t *base = sh ? L.shared_w : L.wbase + uint64_t(it.slot) * L.wstride;
-    const float *wg = reinterpret_cast<const float *>(base) + int64_t(c) * d;
-    const float *wu = wg + int64_t(L.I) * d;
-    float g = 0.f, u = 0.f;
-    for (int k = 0; k < d; ++k) {
-        g = fmaf(x[k], wg[k], g);
-        u = fmaf(x[k], wu[k], u);
-    }
-    reinterpret_cast<float *>(sh ? L.act_s : L.act)[int64_t(it.row0 + r) * L.I + c] = silu(g) * u;
+    const float *w[2];
+    w[0] = reinterpret_cast<const float *>(base) + int64_t(c0) * d;
+    w[1] = w[0] + int64_t(I) * d;
+    float acc[2];
+    f32t::dot<2>(lds, [&](int q) {
+        const int r = it.row0 + min(m0 + q, it.nrows - 1);
+        return reinterpret_cast<const float *>(L.x) + (sh ? int64_t(r) : int64_t(L.perm[r])) * d;
+    }, w, [](int c) { return c; }, d, acc);
+    const int r = m0 + int(threadIdx.x) / f32t::COLS, c = c0 + int(threadIdx.x) % f32t::COLS;
+    if (r < it.nrows)
+        reinterpret_cast<float *>(sh ? L.act_s : L.act)[int64_t(it.row0 + r) * I + c] = silu(acc[0]) * acc[1];
 }
 
 __global__ void __launch_bounds__(256) down_f32_kernel(ExpertLaunch L)
 {
-    const int t = int(blockIdx.x);
-    const WorkItem it = L.items[find_item(L.items, L.n_items, t)];
+    __shared__ f32t::Stage<1> lds;
+    int n_items, n_tiles;
+    const int t = launch_tile(L, n_items, n_tiles);
+    if (t < 0)
+        return;                                   // past the device-built list's tiles
+    const WorkItem it = L.items[find_item(L.items, n_items, t)];
     if (!slot_current(it, L.gen_dev, L.status))
         return;
-    const int local = t - it.tile0;
-    const int nct = L.d / f32p::TC;
-    const int r = (local / nct) * f32p::TR + int(threadIdx.x) / f32p::TC;
-    const int c = (local % nct) * f32p::TC + int(threadIdx.x) % f32p::TC;
-    if (r >= it.nrows)
-        return;
-    const int I = L.I;
-    const int64_t row = it.row0 + r;
+    const int d = L.d, I = L.I;
+    const int local = t - it.tile0, nct = d / f32t::COLS;
+    const int m0 = (local / nct) * f32t::ROWS, c0 = (local % nct) * f32t::COLS;
     const bool sh = it.slot < 0;
-    const float *a = reinterpret_cast<const float *>(sh ? L.act_s : L.act) + row * I;
     const uint8_t *base = sh ? L.shared_w : L.wbase + uint64_t(it.slot) * L.wstride;
-    const float *wd = reinterpret_cast<const float *>(base) + int64_t(2) * I * L.d + int64_t(c) * I;
-    float acc = 0.f;
-    for (int k = 0; k < I; ++k)
-        acc = fmaf(a[k], wd[k], acc);
-    const float w = sh ? 1.0f : L.row_weight[row];
-    static_cast<float *>(sh ? L.ys : L.y)[row * L.d + c] = acc * w;
+    const float *w[1] = {reinterpret_cast<const float *>(base) + int64_t(2) * I * d + int64_t(c0) * I};
+    float acc[1];
+    f32t::dot<1>(lds, [&](int q) {
+        return reinterpret_cast<const float *>(sh ? L.act_s : L.act) +
+               int64_t(it.row0 + min(m0 + q, it.nrows - 1)) * I;
+    }, w, [](int c) { return c; }, I, acc);
+    const int r = m0 + int(threadIdx.x) / f32t::COLS, c = c0 + int(threadIdx.x) % f32t::COLS;
+    if (r < it.nrows) {
+        const int64_t row = it.row0 + r;
+        const float wt = sh ? 1.0f : L.row_weight[row];
+        static_cast<float *>(sh ? L.ys : L.y)[row * d + c] = acc[0] * wt;
+    }
 }
 
 hipError_t launch_gateup_f32(const ExpertLaunch &L, hipStream_t s)

@@ -19,33 +19,29 @@
 #include <algorithm>
 
 #include "common.h"
+#include "dot_f32.h"
 #include "kernels.h"
 
 namespace msi {
 
 // ---------------------------------------------------------------- logits, fp32
-// One thread per (token, expert): sequential fp32 FMA over d.
+// Tiles of 16 tokens x 16 experts (dot_f32.h): sequential fp32 FMA over d.
 __global__ void __launch_bounds__(256) router_logits_f32_kernel(const float *__restrict__ x,
                                                                 const float *__restrict__ wr,
                                                                 const float *__restrict__ bias,
                                                                 float *__restrict__ L, int T, int d, int E)
 {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= int64_t(T) * E)
-        return;
-    const int t = int(i / E), e = int(i % E);
-    const float *xr = x + int64_t(t) * d;
-    const float *wrow = wr + int64_t(e) * d;
-    float acc = 0.f;
-    for (int k = 0; k < d; k += 4) {
-        const float4 a = *reinterpret_cast<const float4 *>(xr + k);
-        const float4 b = *reinterpret_cast<const float4 *>(wrow + k);
-        acc = fmaf(a.x, b.x, acc);
-        acc = fmaf(a.y, b.y, acc);
-        acc = fmaf(a.z, b.z, acc);
-        acc = fmaf(a.w, b.w, acc);
-    }
-    L[i] = acc + (bias ? bias[e] : 0.f);
+    __shared__ f32t::Stage<1> lds;
+    const int nct = (E + f32t::COLS - 1) / f32t::COLS;
+    const int t0 = int(blockIdx.x) / nct * f32t::ROWS, e0 = int(blockIdx.x) % nct * f32t::COLS;
+    const float *w[1] = {wr};
+    float acc[1];
+    // (rows past T and experts past E repeat the last one; they are not stored)
+    f32t::dot<1>(lds, [&](int q) { return x + int64_t(min(t0 + q, T - 1)) * d; }, w,
+                 [&](int c) { return min(e0 + c, E - 1); }, d, acc);
+    const int t = t0 + int(threadIdx.x) / f32t::COLS, e = e0 + int(threadIdx.x) % f32t::COLS;
+    if (t < T && e < E)
+        L[int64_t(t) * E + e] = acc[0] + (bias ? bias[e] : 0.f);
 }
 
 // ---------------------------------------------------------------- top-K
@@ -600,10 +596,10 @@ hipError_t init_route_attributes()
 hipError_t launch_router_logits_f32(const float *x, const float *wr, const float *bias, float *L, int T,
                                     int d, int E, hipStream_t s)
 {
-    const int64_t n = int64_t(T) * E;
-    if (n == 0)
+    if (T == 0 || E == 0)
         return hipSuccess;
-    launch_k(router_logits_f32_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, s, x, wr, bias, L, T, d, E);
+    const unsigned tiles = unsigned((T + f32t::ROWS - 1) / f32t::ROWS) * unsigned((E + f32t::COLS - 1) / f32t::COLS);
+    launch_k(router_logits_f32_kernel, tiles, 256, 0, s, x, wr, bias, L, T, d, E);
     return hipGetLastError();
 }
 
