@@ -11,17 +11,16 @@
 //    nibbles through row-contiguous loads rearranged in LDS (WaveRows); both
 //    operands in pair order (common.h), the codes as the exact bf16 136 + q,
 //    whose offset leaves through the C input as on the tile path.
-//  * tile path: 128 tokens x 128 weight rows per workgroup; A rows, packed
-//    nibbles and scales copied from memory straight into two LDS stage
-//    buffers (three workgroups per CU); the codes enter the MFMA as the exact
-//    bf16 136 + q, and the offset leaves through the C input (-136 times the
-//    A row's block sum, from one more MFMA per A fragment).
+//  * tile path: 64 or 128 tokens x 128 weight rows per workgroup; token rows,
+//    packed nibbles and scales copied from memory straight into two LDS stage
+//    buffers; the codes enter the MFMA as the exact bf16 136 + q, and the
+//    offset leaves through the C input (-136 times the token row's block sum,
+//    from one more MFMA per token fragment).
 #include "common.h"
+#include "gemm_ring.h"
 #include "kernels.h"
 
 namespace msi {
-
-typedef __attribute__((address_space(3))) void lds_void_t;
 
 __device__ __forceinline__ uint32_t q4_matrix_bytes(int rows, int cols)
 {
@@ -351,291 +350,279 @@ static hipError_t launch_down_q4_stream(const ExpertLaunch &L, hipStream_t s)
 // ============================================================== tile path
 
 namespace q4t {
-constexpr int BM = 128, BN = 128, BK = 64, THREADS = 256, NBUF = 2;
-constexpr int A_ROWB = BK * 2;              // bytes of bf16 per staged A row
-constexpr int Q_ROWB = BK / 2;              // bytes of codes per staged weight row
-constexpr int A_BYTES = BM * A_ROWB;        // 16 KiB
-constexpr int Q_BYTES = BN * Q_ROWB;        // 4 KiB
-constexpr int S_BYTES = 2 * BN * (BK / 32) * 2;   // the 512 bytes of scales, then a spare 512 for idle copies
-constexpr int STAGE = A_BYTES + Q_BYTES + S_BYTES;
-constexpr int COPIES = 6;                   // copy instructions per wavefront per stage
-constexpr size_t LDS_BYTES = size_t(NBUF) * STAGE;
+constexpr int BK = 64, ROWB = BK * 2, QROWB = BK / 2;   // K elements per stage; bytes of a staged row of A, of codes
+
+template <bool GU_, int BM_, int TN_, int WR_, int WC_, int WPC_>
+struct Shape {
+    static constexpr bool GU = GU_;
+    static constexpr int BM = BM_, TN = TN_, WR = WR_, WC = WC_, WPC = WPC_;   // rows, weight rows, wavefronts, per CU
+    static constexpr int WAVES = WR * WC, THREADS = 64 * WAVES;
+    static constexpr int MB = BM / WR / 16, NB = TN / WC / 16;
+    static constexpr int A_BYTES = BM * ROWB, Q_BYTES = TN * QROWB, S_BYTES = TN * 4;
+    static constexpr int STAGE = A_BYTES + Q_BYTES + S_BYTES;
+    static constexpr int LA = BM / 8 / WAVES, LQ = TN / 32 / WAVES, NS = TN / 64;
+    static constexpr size_t LDS = size_t(2) * STAGE;
+    static_assert(BM % (8 * WAVES) == 0 && TN % (32 * WAVES) == 0 && NS <= WAVES && LDS * WPC <= 160 * 1024, "");
+};
 }  // namespace q4t
 
-static int tiles_gateup_q4_tile(int nrows, int d, int I)
-{
-    (void)d;
-    return ((nrows + q4t::BM - 1) / q4t::BM) * (I / 64);
-}
-
-static int tiles_down_q4_tile(int nrows, int d, int I)
-{
-    (void)I;
-    return ((nrows + q4t::BM - 1) / q4t::BM) * (d / q4t::BN);
-}
-
-static TileGeom geom_gateup_q4_tile(int d, int I)
-{
-    (void)d;
-    return TileGeom{q4t::BM, I / 64};
-}
-
-static TileGeom geom_down_q4_tile(int d, int I)
-{
-    (void)I;
-    return TileGeom{q4t::BM, d / q4t::BN};
-}
-
-// GATEUP: tile columns 0..63 are gate rows nt*64 .. nt*64+63, columns 64..127 the
-// matching up rows; wavefront (wm, wn) owns rows wm*64.., gate columns
-// wn*32.. and the matching up columns, so SiLU * up forms in registers.
-template <bool GATEUP>
-__global__ void __launch_bounds__(q4t::THREADS, 3) tile_q4_kernel(ExpertLaunch L)
+// Gate/up: tile columns 0 .. TN/2 - 1 are gate rows nt TN/2 .., the rest the
+// matching up rows; wavefront (wm, wn) owns MB 16-row blocks and NB column
+// blocks (gate/up: NB / 2 gate blocks and the matching up blocks, so SiLU * up
+// forms in registers).  Weights are the A operand: a lane's outputs are
+// columns 4g .. 4g + 3 of row r16, stored as 16-byte pieces straight to memory.
+// Stages go from memory straight into two LDS buffers (buffer loads with an
+// LDS destination), one ahead: rows of A as eight 16-byte chunks, chunk c of
+// row r in slot c ^ ((r / 2) % 8), codes as two chunks, chunk c of row r in slot
+// c ^ ((r / 8) % 2), which puts the 16 rows of each fragment read on distinct
+// banks, and the rows' two scales.  The codes enter the MFMA as 136 + q; the
+// -136 * (block sum of the token row) that takes the offset back out comes from
+// one more MFMA per token fragment, against a fragment of -136, and is the C
+// input of that fragment's block partials.
+template <class S>
+__global__ void __launch_bounds__(S::THREADS, S::WPC *S::WAVES / 4) tile_q4_kernel(ExpertLaunch L)
 {
     using namespace q4t;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds8[];
+    constexpr bool GU = S::GU;
+    constexpr int BM = S::BM, TN = S::TN, WAVES = S::WAVES, MB = S::MB, NB = S::NB, STAGE = S::STAGE;
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds8[];
     int n_items, n_tiles;
     const int t = launch_tile(L, n_items, n_tiles);
     if (t < 0)
         return;                                   // past the device-built list's tiles
     const WorkItem it = L.items[find_item(L.items, n_items, t)];
-    if (!slot_current(it, L.gen_dev, L.status))
-        return;
+    const uint32_t gnow = slot_gen_now(it, L.gen_dev);   // compared before the stores
     const bool sh = it.slot < 0;
     const int d = L.d, I = L.I;
-    const int K = GATEUP ? d : I;
-    const int ntn = GATEUP ? I / 64 : d / BN;
+    const int K = GU ? d : I;
+    const int ntn = GU ? I / (TN / 2) : d / TN;
     const int local = t - it.tile0;
     const int m0 = (local / ntn) * BM;
     const int nt = local % ntn;
+    const int valid = min(BM, it.nrows - m0);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (uniform: copy destinations and resources)
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave / S::WC, wn = wave % S::WC;
+    const int r16 = lane & 15, g = lane >> 4;
 
-    const uint16_t *abase = reinterpret_cast<const uint16_t *>(GATEUP ? L.x : (sh ? L.act_s : L.act));
-    const int32_t *perm = (GATEUP && !sh) ? L.perm : nullptr;
     const uint8_t *obj = sh ? L.shared_w : L.wbase + uint64_t(it.slot) * L.wstride;
     const uint32_t mbytes = q4_matrix_bytes(I, d);
-
-    // Stage copies go from memory straight into two LDS stage buffers (buffer loads with an
-    // LDS destination, no register staging).  Per stage and wavefront: four 1 KiB copies of A rows (lane l
-    // of copy i brings row 8 (4 i + w) + l / 8 into slot l % 8 of its 128-byte LDS row, the 16-byte chunk
-    // (l % 8) ^ aswz(row) of the row's 64 elements), one of weight codes (row 32 w + l / 2, slot l % 2 =
-    // chunk (l % 2) ^ bit 3 of the row) and one of scales (4 bytes: row 64 w + l; wavefronts 2 and 3 copy
-    // nothing into a spare region, so every wavefront waits on the same counts).  The slot permutations put
-    // the 16 rows of each fragment read on distinct banks.
-    auto aswz = [](int r) { return (r >> 1) & 7; };
-    const __amdgpu_buffer_rsrc_t ar =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(abase), 0, 0x7fffffff, 0x00020000u);
-    const __amdgpu_buffer_rsrc_t wr_ = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(obj), 0, 0x7fffffff,
-                                                                         0x00020000u);
-    const __amdgpu_buffer_rsrc_t sr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(obj), 0,
-                                                                        wave < 2 ? 0x7fffffff : 0, 0x00020000u);
-    uint32_t aoff[4];
+    // byte offset, from the object, of tile column c's matrix and its row there
+    auto col_matrix = [&](int c) -> uint32_t { return GU ? (c < TN / 2 ? 0u : mbytes) : 2 * mbytes; };
+    auto col_row = [&](int c) -> uint32_t {
+        return GU ? uint32_t(nt * (TN / 2) + (c < TN / 2 ? c : c - TN / 2)) : uint32_t(nt * TN + c);
+    };
+    [[maybe_unused]] const void *abase = GU ? L.x
+                                            : static_cast<const uint8_t *>(sh ? L.act_s : L.act) +
+                                                  (int64_t(it.row0) + m0) * int64_t(I) * 2;
+    uint32_t aoff[S::LA], qoff[S::LQ];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = 8 * (4 * i + wave) + (lane >> 3);
-        int64_t src = 0;
-        if (m0 + r < it.nrows)
-            src = perm ? int64_t(perm[it.row0 + m0 + r]) : int64_t(it.row0 + m0 + r);
-        aoff[i] = uint32_t(src * K) * 2u + uint32_t(16 * ((lane & 7) ^ aswz(r)));
+    for (int i = 0; i < S::LA; ++i) {
+        const int r = 8 * (WAVES * i + wave) + (lane >> 3);
+        const int m = m0 + min(r, valid - 1);     // rows past the end repeat the last one and are never stored
+        const uint32_t src = !GU ? uint32_t(m - m0) : sh ? uint32_t(it.row0 + m) : uint32_t(L.perm[it.row0 + m]);
+        aoff[i] = src * uint32_t(K * 2) + uint32_t(((lane & 7) ^ ((r >> 1) & 7)) << 4);
     }
-    auto weight_row = [&](int c) -> int {          // tile column -> matrix row
-        if (GATEUP)
-            return (c < 64 ? 0 : I) + nt * 64 + (c & 63);
-        return nt * BN + c;
-    };
-    // (a tile column's matrix: gate rows, then up rows, for gate/up; the down matrix for down)
-    auto row_base = [&](int c) -> uint32_t {
-        const int wrw = weight_row(c);
-        const uint32_t mat = GATEUP ? (wrw >= I ? mbytes : 0u) : 2u * mbytes;
-        return mat + uint32_t(GATEUP ? (wrw >= I ? wrw - I : wrw) : wrw) * uint32_t(K / 2);
-    };
-    auto scale_base = [&](int c) -> uint32_t {
-        const int wrw = weight_row(c);
-        const uint32_t mat = GATEUP ? (wrw >= I ? mbytes : 0u) : 2u * mbytes;
-        const int rows = GATEUP ? I : d;
-        return mat + uint32_t(rows) * uint32_t(K / 2) + uint32_t(GATEUP ? (wrw >= I ? wrw - I : wrw) : wrw) *
-                                                            uint32_t(K / 32) * 2u;
-    };
-    const int qr = 32 * wave + (lane >> 1);
-    const uint32_t qoff = row_base(qr) + uint32_t(16 * ((lane & 1) ^ ((qr >> 3) & 1)));
-    const uint32_t soff = wave < 2 ? scale_base(64 * wave + lane) : 0u;
-    auto issue = [&](int k0, int buf, bool real) {
-        uint8_t *st = lds8 + buf * STAGE;
-        const __amdgpu_buffer_rsrc_t none = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(obj), 0, 0,
-                                                                              0x00020000u);
-#if defined(__HIP_DEVICE_COMPILE__)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(real ? ar : none, (lds_void_t *)(st + (4 * i + wave) * 1024), 16,
-                                                     aoff[i], k0 * 2, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(real ? wr_ : none, (lds_void_t *)(st + A_BYTES + wave * 1024), 16,
-                                                 qoff, k0 / 2, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(real ? sr : none, (lds_void_t *)(st + A_BYTES + Q_BYTES + wave * 256),
-                                                 4, soff, k0 / 16, 0, 0);
+    for (int i = 0; i < S::LQ; ++i) {
+        const int c = 32 * (WAVES * i + wave) + (lane >> 1);
+        qoff[i] = col_matrix(c) + col_row(c) * uint32_t(K / 2) + uint32_t(16 * ((lane & 1) ^ ((c >> 3) & 1)));
+    }
+    const int sc_col = 64 * (wave % S::NS) + lane;
+    [[maybe_unused]] const uint32_t soff = col_matrix(sc_col) + uint32_t(GU ? I : d) * uint32_t(K / 2) +
+                                           col_row(sc_col) * uint32_t(K / 32) * 2u;
+    auto issue = [&](int stage, int buf) {
+        uint8_t *st = lds8 + buf * STAGE;
+#if defined(__HIP_DEVICE_COMPILE__)
+        const __amdgpu_buffer_rsrc_t ar =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(abase), 0, 0x7fffffff, 0x00020000u);
+        const __amdgpu_buffer_rsrc_t wr_ =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(obj), 0, 0x7fffffff, 0x00020000u);
+#pragma unroll
+        for (int i = 0; i < S::LA; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ar, (lds_void_t *)(st + (WAVES * i + wave) * 1024), 16, aoff[i],
+                                                     stage * ROWB, 0, 0);
+#pragma unroll
+        for (int i = 0; i < S::LQ; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr_, (lds_void_t *)(st + S::A_BYTES + (WAVES * i + wave) * 1024),
+                                                     16, qoff[i], stage * QROWB, 0, 0);
+        if (wave < S::NS)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr_, (lds_void_t *)(st + S::A_BYTES + S::Q_BYTES + wave * 256), 4,
+                                                     soff, stage * 4, 0, 0);
 #else
-        (void)st, (void)none, (void)k0, (void)real;
+        (void)st, (void)stage;
 #endif
     };
 
-    f32x4 acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int r16 = lane & 15, g = lane >> 4;
     auto col_of = [&](int nb) -> int {              // tile column block of this wavefront
-        if (GATEUP)
-            return nb < 2 ? wn * 32 + nb * 16 : 64 + wn * 32 + (nb - 2) * 16;
-        return wn * 64 + nb * 16;
+        if (GU)
+            return nb < NB / 2 ? (wn * (NB / 2) + nb) * 16 : TN / 2 + (wn * (NB / 2) + nb - NB / 2) * 16;
+        return (wn * NB + nb) * 16;
     };
-    // The codes enter the MFMA as 136 + q; the -136 * (block sum of the A row) that takes the offset back
-    // out comes from one more MFMA per A fragment, against a fragment of -136, and is the C input of that
-    // fragment's four block partials.
+    f32x4 acc[NB][MB];
+#pragma unroll
+    for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int b = 0; b < MB; ++b)
+            acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
     const bf16x8 neg136 = __builtin_bit_cast(bf16x8, u32x4{0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u});
     auto compute = [&](int buf) {
         const uint8_t *st = lds8 + buf * STAGE;
-        const uint8_t *q = st + A_BYTES;
-        const uint16_t *sc = reinterpret_cast<const uint16_t *>(st + A_BYTES + Q_BYTES);
 #pragma unroll
         for (int kb = 0; kb < BK / 32; ++kb) {
-            uint32_t cw[4];
-            uint16_t sr16[4];
+            uint32_t cw[NB];
+            u32x4 sc[NB];                           // the scales of rows 4g .. 4g + 3, both blocks
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-                const int c = col_of(nb) + r16;                    // B fragment: weight row c
-                cw[nb] = *reinterpret_cast<const uint32_t *>(q + c * Q_ROWB + 16 * (kb ^ ((c >> 3) & 1)) + 4 * g);
-                sr16[nb] = sc[c * 2 + kb];
+            for (int nb = 0; nb < NB; ++nb) {
+                const int c = col_of(nb) + r16;                    // A fragment: weight row c
+                cw[nb] = *reinterpret_cast<const uint32_t *>(st + S::A_BYTES + c * QROWB + 16 * (kb ^ ((c >> 3) & 1)) +
+                                                             4 * g);
+                sc[nb] = *reinterpret_cast<const u32x4 *>(st + S::A_BYTES + S::Q_BYTES + (col_of(nb) + 4 * g) * 4);
             }
-            bf16x8 af[4];
-            f32x4 corr[4];
+            bf16x8 af[MB];
+            f32x4 corr[MB];
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
-                const int r = wm * 64 + mb * 16 + r16;
-                af[mb] = as_bf16x8(*reinterpret_cast<const u32x4 *>(st + r * A_ROWB + 16 * ((4 * kb + g) ^ aswz(r))));
-                corr[mb] = mfma16(af[mb], neg136, f32x4{0.f, 0.f, 0.f, 0.f});
+            for (int mb = 0; mb < MB; ++mb) {
+                const int r = (wm * MB + mb) * 16 + r16;
+                af[mb] = as_bf16x8(*reinterpret_cast<const u32x4 *>(st + r * ROWB + (((4 * kb + g) ^ ((r >> 1) & 7)) << 4)));
+                corr[mb] = mfma16(neg136, af[mb], f32x4{0.f, 0.f, 0.f, 0.f});
             }
-            bf16x8 bq[4];
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
-                bq[nb] = unpack_q4_136(cw[nb]);
+            for (int nb = 0; nb < NB; ++nb) {
+                const bf16x8 w = unpack_q4_136(cw[nb]);
+                f32x4 part[MB];
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-                const float s = half_to_float(sr16[nb]);          // output column of this lane = c
-                f32x4 part[4];
+                for (int mb = 0; mb < MB; ++mb)
+                    part[mb] = mfma16(w, af[mb], corr[mb]);
 #pragma unroll
-                for (int mb = 0; mb < 4; ++mb)
-                    part[mb] = mfma16(af[mb], bq[nb], corr[mb]);
+                for (int i = 0; i < 4; ++i) {
+                    const float s = half_to_float(uint16_t(sc[nb][i] >> (16 * kb)));
 #pragma unroll
-                for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr)
-                        acc[mb][nb][rr] = fmaf(s, part[mb][rr], acc[mb][nb][rr]);
+                    for (int mb = 0; mb < MB; ++mb)
+                        acc[nb][mb][i] = fmaf(s, part[mb][i], acc[nb][mb][i]);
+                }
             }
         }
     };
 
     const int nk = K / BK;
-    constexpr int AHEAD = NBUF - 1;                            // stages in flight beside the one computed
-#pragma unroll
-    for (int j = 0; j < AHEAD; ++j)
-        issue(j * BK, j, j < nk);
+    issue(0, 0);
     for (int kt = 0; kt < nk; ++kt) {
-        __builtin_amdgcn_s_waitcnt(VMCNT_WAIT(COPIES * (AHEAD - 1)));   // this stage landed
-        __builtin_amdgcn_s_barrier();                          // ... for every wavefront; the buffer refilled
-        asm volatile("" ::: "memory");                         //     next was last read one stage ago
-        issue((kt + AHEAD) * BK, (kt + AHEAD) % NBUF, kt + AHEAD < nk);
-        compute(kt % NBUF);
+        __builtin_amdgcn_s_waitcnt(VMCNT_WAIT(0));  // this stage landed ...
+        __builtin_amdgcn_s_barrier();               // ... for every wavefront; the other buffer was last read
+        asm volatile("" ::: "memory");              //     one stage ago
+        if (kt + 1 < nk)
+            issue(kt + 1, (kt + 1) & 1);
+        compute(kt & 1);
     }
+    if (!slot_gen_ok(it, gnow, L.status))
+        return;
 
-    // Epilogue through LDS (the stage buffers are free once every wavefront has left the K loop): each lane
-    // writes its outputs, rows 4g + rr of each 16x16 block in column r16, as bf16 into a [128][OUTW + 8]
-    // tile, then every thread stores whole 16-byte pieces of the tile's rows.  The row weights of the
-    // lane's 16 rows are read first, all at once.
-    constexpr int OUTW = GATEUP ? 64 : BN;         // output columns of the tile
-    constexpr int LDO = OUTW + 8;                  // bf16 per LDS output row (16 bytes of padding)
-    float rwv[4][4];
+    // ---- epilogue: lane holds columns 4g .. 4g + 3 of each block of row r16; two blocks at a time are regrouped
+    // so that each lane stores 16 contiguous bytes
+    const int64_t rowbase = int64_t(it.row0) + m0;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < MB; ++mb) {
+        const int row = (wm * MB + mb) * 16 + r16;
+        const bool in = row < valid;
+        constexpr int OB = GU ? NB / 2 : NB;        // output blocks
+        uint32_t lo[OB], hi[OB];
+        if constexpr (GU) {
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const int row = wm * 64 + mb * 16 + 4 * g + rr;
-            rwv[mb][rr] = (GATEUP || sh || m0 + row >= it.nrows) ? 1.0f : L.row_weight[int64_t(it.row0) + m0 + row];
-        }
-    static_assert(size_t(BM) * LDO * 2 <= LDS_BYTES, "output tile fits the stage buffers");
-    __builtin_amdgcn_s_waitcnt(VMCNT_WAIT(0));    // the last (idle) stage copies have written LDS too
-    __syncthreads();
-    uint16_t *ot = reinterpret_cast<uint16_t *>(lds8);
+            for (int nb = 0; nb < OB; ++nb) {
+                float v[4];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+                for (int i = 0; i < 4; ++i)
+                    v[i] = silu_hw(acc[nb][mb][i]) * acc[nb + OB][mb][i];
+                lo[nb] = pack_bf16x2_hw(v[0], v[1]);
+                hi[nb] = pack_bf16x2_hw(v[2], v[3]);
+            }
+        } else {
+            const float w = (sh || !in) ? 1.0f : L.row_weight[rowbase + row];
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            uint16_t *orow_l = ot + (wm * 64 + mb * 16 + 4 * g + rr) * LDO;
-            if (GATEUP) {
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb)
-                    orow_l[wn * 32 + nb * 16 + r16] = f32_to_bf16(silu(acc[mb][nb][rr]) * acc[mb][nb + 2][rr]);
-            } else {
-#pragma unroll
-                for (int nb = 0; nb < 4; ++nb)
-                    orow_l[wn * 64 + nb * 16 + r16] = f32_to_bf16(acc[mb][nb][rr] * rwv[mb][rr]);
+            for (int nb = 0; nb < OB; ++nb) {
+                lo[nb] = pack_bf16x2_hw(acc[nb][mb][0] * w, acc[nb][mb][1] * w);
+                hi[nb] = pack_bf16x2_hw(acc[nb][mb][2] * w, acc[nb][mb][3] * w);
             }
         }
-    __syncthreads();
-    constexpr int PPR = OUTW / 8;                  // 16-byte pieces per tile row
-    uint16_t *obase = GATEUP ? reinterpret_cast<uint16_t *>(sh ? L.act_s : L.act) + nt * 64
-                             : static_cast<uint16_t *>(sh ? L.ys : L.y) + nt * BN;
-    const int ostride = GATEUP ? I : d;
+        uint16_t *dst = GU ? static_cast<uint16_t *>(sh ? L.act_s : L.act) + (rowbase + row) * I + nt * (TN / 2)
+                           : static_cast<uint16_t *>(sh ? L.ys : L.y) + (rowbase + row) * d + nt * TN;
+        dst += wn * OB * 16;
+        if constexpr (OB == 1) {
+            if (in)
+                *reinterpret_cast<uint2 *>(dst + 4 * g) = make_uint2(lo[0], hi[0]);
+        } else {
 #pragma unroll
-    for (int k = 0; k < BM * PPR / THREADS; ++k) {
-        const int pidx = k * THREADS + tid, row = pidx / PPR, pc = pidx % PPR;
-        if (m0 + row < it.nrows)
-            *reinterpret_cast<u32x4 *>(obase + (int64_t(it.row0) + m0 + row) * ostride + pc * 8) =
-                *reinterpret_cast<const u32x4 *>(ot + row * LDO + pc * 8);
+            for (int k = 0; k < OB / 2; ++k) {
+                const uint4 v = gather16(lo[2 * k], hi[2 * k], lo[2 * k + 1], hi[2 * k + 1]);
+                if (in)
+                    *reinterpret_cast<uint4 *>(dst + 32 * k + 8 * g) = v;
+            }
+        }
     }
 }
 
-static hipError_t launch_gateup_q4_tile(const ExpertLaunch &L, hipStream_t s)
+template <class S>
+static int q4_tiles(int nrows, int d, int I)
+{
+    return (nrows + S::BM - 1) / S::BM * (S::GU ? I / (S::TN / 2) : d / S::TN);
+}
+
+template <class S>
+static TileGeom q4_geom(int d, int I)
+{
+    return TileGeom{S::BM, S::GU ? I / (S::TN / 2) : d / S::TN};
+}
+
+template <class S>
+static hipError_t launch_q4_tile(const ExpertLaunch &L, hipStream_t s)
 {
     if (L.n_tiles == 0)
         return hipSuccess;
-    launch_k(tile_q4_kernel<true>, L.n_tiles, q4t::THREADS, q4t::LDS_BYTES, s, L);
+    launch_k(tile_q4_kernel<S>, L.n_tiles, S::THREADS, S::LDS, s, L);
     return hipGetLastError();
 }
 
-static hipError_t launch_down_q4_tile(const ExpertLaunch &L, hipStream_t s)
-{
-    if (L.n_tiles == 0)
-        return hipSuccess;
-    launch_k(tile_q4_kernel<false>, L.n_tiles, q4t::THREADS, q4t::LDS_BYTES, s, L);
-    return hipGetLastError();
-}
+using Q4GateSmall = q4t::Shape<true, 64, 128, 1, 4, 4>;
+using Q4GateBig = q4t::Shape<true, 128, 128, 2, 2, 2>;
+using Q4Down = q4t::Shape<false, 64, 128, 1, 2, 6>;
 
-template <int R>
-static const KernelSet q4_set{tiles_gateup_q4_tile, tiles_gateup_q4_stream<R>, tiles_down_q4_tile,
-                              tiles_down_q4_stream<R>, geom_gateup_q4_tile, geom_down_q4_tile,
-                              launch_gateup_q4_tile, launch_gateup_q4_stream<R>, launch_down_q4_tile,
-                              launch_down_q4_stream<R>};
+template <class G, int R>
+static const KernelSet q4_set{q4_tiles<G>, tiles_gateup_q4_stream<R>, q4_tiles<Q4Down>, tiles_down_q4_stream<R>,
+                              q4_geom<G>, q4_geom<Q4Down>,
+                              launch_q4_tile<G>, launch_gateup_q4_stream<R>,
+                              launch_q4_tile<Q4Down>, launch_down_q4_stream<R>};
 
-// R of the stream kernels by the routed rows, which bound the launch's items:
-// from 32 on its workgroups fill the chip with R = 2 as well.  The two are
-// bit-identical.  Measured (MI355X, d 2048, I 512, K 10; gate/up + down, us,
-// R = 1, R = 2; in parentheses codes converted one by one, R = 1): T 1 6.8+5.2,
-// 9.1+6.1 (8.3+5.5); T 4 13.5+9.5, 13.6+9.1 (16.7+9.3); T 16 39.7+25.3,
-// 37.6+21.6 (48.2+29.1); T 1013 129+82, 116+66 (148+91).
-const KernelSet &q4_kernels(uint64_t rows, uint64_t)
+// Tile forms by the mean rows per expert, R of the stream kernels by the
+// routed rows, which bound the launch's items: from 32 on its workgroups fill
+// the chip with R = 2 as well.  All forms are bit-identical (the same chain of
+// operations per output), so the choice is the launch's.
+// Measured (MI355X, E 512, d 2048, I 512, K 10, us):
+//   stream gate/up + down, R = 1, R = 2 (in parentheses codes converted one by
+//   one, R = 1): T 1 6.8+5.2, 9.1+6.1 (8.3+5.5); T 4 13.5+9.5, 13.6+9.1
+//   (16.7+9.3); T 16 39.7+25.3, 37.6+21.6 (48.2+29.1); T 1013 129+82, 116+66
+//   (148+91);
+//   tile gate/up 64 x 128, 128 x 128: mean rows 40 282, 401; 80 457, 411; 640
+//   2499, 2305; down 64 x 128 by two wavefronts, 128 x 128: 40 127, 223; 80 227,
+//   241; 640 1279, 1407 (in one form of 128 x 128 with an epilogue through LDS:
+//   394, 425, 2380 and 236, 263, 1475).
+const KernelSet &q4_kernels(uint64_t rows, uint64_t E)
 {
-    return rows >= 32 ? q4_set<2> : q4_set<1>;
+    if (rows < 32)
+        return q4_set<Q4GateSmall, 1>;
+    return rows <= 64 * E ? q4_set<Q4GateSmall, 2> : q4_set<Q4GateBig, 2>;
 }
 
 hipError_t init_q4_attributes()
 {
-    hipError_t e = allow_large_lds(reinterpret_cast<const void *>(&tile_q4_kernel<true>));
-    if (e == hipSuccess)
-        e = allow_large_lds(reinterpret_cast<const void *>(&tile_q4_kernel<false>));
-    return e;
+    for (const void *k : {reinterpret_cast<const void *>(&tile_q4_kernel<Q4GateSmall>),
+                          reinterpret_cast<const void *>(&tile_q4_kernel<Q4GateBig>),
+                          reinterpret_cast<const void *>(&tile_q4_kernel<Q4Down>)}) {
+        const hipError_t e = allow_large_lds(k);
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace msi
