@@ -271,9 +271,10 @@ typedef enum {
     MSI_K_TOPK = 1,
     MSI_K_PERMUTE = 2,
     MSI_K_GATEUP_TILE = 3,     /* routed experts, tiled MFMA path                 */
-    MSI_K_GATEUP_STREAM = 4,   /* routed experts, weight-streaming path           */
+    MSI_K_GATEUP_STREAM = 4,   /* routed experts, weight-streaming path; also a
+                                  launch that runs both paths' lists             */
     MSI_K_DOWN_TILE = 5,
-    MSI_K_DOWN_STREAM = 6,
+    MSI_K_DOWN_STREAM = 6,     /* as GATEUP_STREAM                               */
     MSI_K_EXPERT_F32 = 7,      /* fp32 layers, gate/up and down                   */
     MSI_K_SHARED = 8,          /* shared expert, gate/up and down                 */
     MSI_K_COMBINE = 9,

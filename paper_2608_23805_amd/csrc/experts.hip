@@ -15,6 +15,7 @@
 // to bf16 once (fp32 throughout for fp32 layers).
 #include "common.h"
 #include "dot_f32.h"
+#include "gemm_mid.h"
 #include "kernels.h"
 
 namespace msi {
@@ -53,19 +54,19 @@ struct StreamTile {
     bool valid;
 };
 
-__device__ __forceinline__ StreamTile stream_tile(const ExpertLaunch &L, int per_item)
+__device__ __forceinline__ StreamTile stream_tile(const ExpertLaunch &L, int per_item, int b, int n_blocks)
 {
     StreamTile st{};
     if (L.direct.demand) {
         int i;
-        direct_tile(int(blockIdx.x), per_item, i, st.local);
+        direct_tile(b, per_item, i, st.local);
         if (!direct_item(L.direct, i, per_item, L.status, st.it))
             return st;
         st.valid = st.it.nrows > 0;       // nrows 0: unpublished expert, no work
         return st;
     }
     int n_items, n_tiles;
-    const int t = launch_tile(L, n_items, n_tiles);
+    const int t = launch_tile(L, b, n_blocks, n_items, n_tiles);
     const int i = t / per_item;
     if (t < 0 || i >= n_items)
         return st;
@@ -121,13 +122,16 @@ __device__ __forceinline__ void lds_wait()
 // grid many times larger than the number of resident workgroups, so the last
 // partial round of the launch is short.
 template <int U, int NB>
-__global__ void __launch_bounds__(256, 3) stream_gateup_kernel(ExpertLaunch L)
+struct StreamGateUp {
+static constexpr int SL = U / 2;                  // slabs per matrix per batch
+static constexpr int REGION = 2 * SL * slab::BYTES;
+static constexpr size_t LDS = stream::WAVES * REGION + 3 * 2 * 64 * sizeof(f32x4);
+static constexpr int WAVES_PER_SIMD = 3;
+static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int n_blocks, uint8_t *lds)
 {
-    constexpr int SL = U / 2;                     // slabs per matrix per batch
-    __shared__ f32x4 red[3][2][64];
-    __shared__ __attribute__((aligned(16))) uint8_t tr[stream::WAVES][2 * SL * slab::BYTES];
+    f32x4 (*red)[2][64] = reinterpret_cast<f32x4 (*)[2][64]>(lds + stream::WAVES * REGION);
     const int d = L.d, I = L.I;
-    const StreamTile st = stream_tile(L, I / stream::ROWS);
+    const StreamTile st = stream_tile(L, I / stream::ROWS, block, n_blocks);
     if (!st.valid)
         return;
     const WorkItem &it = st.it;
@@ -145,7 +149,7 @@ __global__ void __launch_bounds__(256, 3) stream_gateup_kernel(ExpertLaunch L)
     const uint16_t *gp0 = w0 + slab::src(lane, 0, d), *gp1 = w0 + slab::src(lane, 1, d);
     const int64_t um = int64_t(I) * d;            // Wu follows Wg
     const bool live = j < n;
-    uint8_t *t = tr[wave];
+    uint8_t *t = lds + wave * REGION;
 
     // This lane's token (the shared expert's rows are the tokens in order),
     // read before the weights are issued: memory reads complete in order, so
@@ -239,6 +243,14 @@ __global__ void __launch_bounds__(256, 3) stream_gateup_kernel(ExpertLaunch L)
         *reinterpret_cast<uint2 *>(act) = v;
     }
 }
+};
+
+template <int U, int NB>
+__global__ void __launch_bounds__(256, 3) stream_gateup_kernel(ExpertLaunch L)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[StreamGateUp<U, NB>::LDS];
+    StreamGateUp<U, NB>::run(L, int(blockIdx.x), int(gridDim.x), lds);
+}
 
 // Down, stream path: a workgroup owns 64 output columns (16 per wavefront)
 // over all of I, in chunks of NB batches of 4 K steps (2 slabs of Wd rows,
@@ -249,12 +261,15 @@ __global__ void __launch_bounds__(256, 3) stream_gateup_kernel(ExpertLaunch L)
 // read its last row, whose outputs are never stored), so no workgroup
 // barrier or LDS staging comes before the first MFMA.
 template <int NB>
-__global__ void __launch_bounds__(256, 4) stream_down_kernel(ExpertLaunch L)
+struct StreamDown {
+static constexpr int U = 4, SL = U / 2;
+static constexpr int REGION = SL * slab::BYTES;
+static constexpr size_t LDS = stream::WAVES * REGION;
+static constexpr int WAVES_PER_SIMD = 4;
+static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int n_blocks, uint8_t *lds)
 {
-    constexpr int U = 4, SL = U / 2;
-    __shared__ __attribute__((aligned(16))) uint8_t tr[stream::WAVES][SL * slab::BYTES];
     const int d = L.d, I = L.I;
-    const StreamTile st = stream_tile(L, d / (stream::WAVES * stream::ROWS));
+    const StreamTile st = stream_tile(L, d / (stream::WAVES * stream::ROWS), block, n_blocks);
     if (!st.valid)
         return;
     const WorkItem &it = st.it;
@@ -272,7 +287,7 @@ __global__ void __launch_bounds__(256, 4) stream_down_kernel(ExpertLaunch L)
     const uint16_t *ap = reinterpret_cast<const uint16_t *>(sh ? L.act_s : L.act) +
                          int64_t(it.row0 + min(j, n - 1)) * I + kg;
     const bool live = j < n;
-    uint8_t *t = tr[wave];
+    uint8_t *t = lds + wave * REGION;
     auto load_w = [&](u32x4(&dst)[SL][2], u32x4(&adst)[U], int k0) {
 #pragma unroll
         for (int s = 0; s < SL; ++s) {
@@ -319,6 +334,14 @@ __global__ void __launch_bounds__(256, 4) stream_down_kernel(ExpertLaunch L)
             make_uint2(pack_bf16x2(acc[0] * wt, acc[1] * wt), pack_bf16x2(acc[2] * wt, acc[3] * wt));
     }
 }
+};
+
+template <int NB>
+__global__ void __launch_bounds__(256, 4) stream_down_kernel(ExpertLaunch L)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[StreamDown<NB>::LDS];
+    StreamDown<NB>::run(L, int(blockIdx.x), int(gridDim.x), lds);
+}
 
 hipError_t launch_gateup_stream(const ExpertLaunch &L, hipStream_t s)
 {
@@ -349,6 +372,26 @@ hipError_t launch_down_stream(const ExpertLaunch &L, hipStream_t s)
     else
         launch_k(stream_down_kernel<1>, L.n_tiles, 256, 0, s, L);
     return hipGetLastError();
+}
+
+// The 64-row tiles and the stream list in one launch (both_kernel).  Measured
+// (MI355X, E 512, d 2048, I 512, K 10; gate/up, us): two launches 15.7 + 276
+// (128 tokens), 17.6 + 302 (509), 146 + 200 (800); together 282, 313, 340.
+// The tiles keep two stage buffers here, not three: 49 KB of LDS, so that
+// three workgroups of either list share a CU (the stream list's own three).
+// Down stays in two launches: its stream kernel runs four workgroups per CU
+// and lost more at three (203 against 9.6 + 186 us at 509 tokens).
+hipError_t launch_gateup_both(const ExpertLaunch &T, const ExpertLaunch &S, hipStream_t s)
+{
+    using Tile = MidTile<RingMode::GateUp, Mid64Both>;
+    const int kq = S.d / 4;
+    if (kq % 512 == 0)
+        return launch_both<Tile, StreamGateUp<4, 4>>(T, S, s);
+    if (kq % 256 == 0)
+        return launch_both<Tile, StreamGateUp<4, 2>>(T, S, s);
+    if (kq % 128 == 0)
+        return launch_both<Tile, StreamGateUp<4, 1>>(T, S, s);
+    return launch_both<Tile, StreamGateUp<2, 1>>(T, S, s);
 }
 
 // ============================================================== f32 path

@@ -105,16 +105,16 @@ __device__ __forceinline__ K6Planes k6_planes(const uint8_t *m, uint32_t rows, u
 
 // Tile of a launch and its item (device-built decode list, device-built
 // prefill list, or host list), as the 4-bit kernels find theirs.
-__device__ __forceinline__ bool kq_tile(const ExpertLaunch &L, int per_item, int &t, WorkItem &it)
+__device__ __forceinline__ bool kq_tile(const ExpertLaunch &L, int per_item, int b, int n_blocks, int &t, WorkItem &it)
 {
     if (L.direct.demand) {
         int i, local;
-        direct_tile(int(blockIdx.x), per_item, i, local);
+        direct_tile(b, per_item, i, local);
         t = i * per_item + local;
         return direct_item(L.direct, i, per_item, L.status, it);
     }
     int n_items, n_tiles;
-    t = launch_tile(L, n_items, n_tiles);
+    t = launch_tile(L, b, n_blocks, n_items, n_tiles);
     if (t < 0)
         return false;
     it = L.items[find_item(L.items, n_items, t)];
@@ -145,17 +145,20 @@ constexpr int WAVES = 4, ROWS = 16;
 // coefficients back.  R = 2 where a launch has many items: a token fragment
 // (1 KiB from 16 rows) then serves twice the codes (see the 4-bit kernels).
 template <int CH, int R>
-__global__ void __launch_bounds__(256, R == 1 ? 3 : 2) stream_gateup_kq_kernel(ExpertLaunch L)
+struct KqStreamGateUp {
+using Rows = WaveRows<16 * CH>;
+static constexpr int NM = 2 * R;                       // 16-row groups: R of Wg, then R of Wu
+static constexpr int REGION = NM * 16 * Rows::RS > NM * 1024 ? NM * 16 * Rows::RS : NM * 1024;
+static constexpr size_t LDS = kqs::WAVES * (REGION + CH * NM * 16 * sizeof(float2));
+static constexpr int WAVES_PER_SIMD = 3;
+static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int n_blocks, uint8_t *lds)
 {
-    using Rows = WaveRows<16 * CH>;
-    constexpr int NM = 2 * R;                          // 16-row groups: R of Wg, then R of Wu
-    constexpr int REGION = NM * 16 * Rows::RS > NM * 1024 ? NM * 16 * Rows::RS : NM * 1024;
-    // a wavefront's rows, then (its own part) its partial sums
-    __shared__ __attribute__((aligned(16))) uint8_t wst[kqs::WAVES][REGION];
-    __shared__ float2 coef[kqs::WAVES][CH][NM][16];    // {a, b} of block u, row group m, row r
+    // a wavefront's rows, then (its own part) its partial sums; {a, b} of block u, row group m, row r
+    uint8_t (*wst)[REGION] = reinterpret_cast<uint8_t (*)[REGION]>(lds);
+    float2 (*coef)[CH][NM][16] = reinterpret_cast<float2 (*)[CH][NM][16]>(lds + kqs::WAVES * REGION);
     int t;
     WorkItem it;
-    if (!kq_tile(L, L.I / (kqs::ROWS * R), t, it) || it.nrows == 0 ||
+    if (!kq_tile(L, L.I / (kqs::ROWS * R), block, n_blocks, t, it) || it.nrows == 0 ||
         !slot_current(it, L.gen_dev, L.status))      // nrows 0: unpublished expert, no work
         return;
     static_assert(CH <= 8, "a chunk stays within one super-block");
@@ -262,6 +265,14 @@ __global__ void __launch_bounds__(256, R == 1 ? 3 : 2) stream_gateup_kq_kernel(E
             if (4 * g + i < n)
                 act[int64_t(4 * g + i) * I + 16 * m] = f32_to_bf16(silu(acc[m][i]) * acc[m + R][i]);
 }
+};
+
+template <int CH, int R>
+__global__ void __launch_bounds__(256, R == 1 ? 3 : 2) stream_gateup_kq_kernel(ExpertLaunch L)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[KqStreamGateUp<CH, R>::LDS];
+    KqStreamGateUp<CH, R>::run(L, int(blockIdx.x), int(gridDim.x), lds);
+}
 
 // Down, k6 stream path: a workgroup owns 64 output columns (16 per wavefront)
 // over all of I, in groups of G super-blocks whose low nibbles and high parts
@@ -274,16 +285,19 @@ __global__ void __launch_bounds__(256, R == 1 ? 3 : 2) stream_gateup_kq_kernel(E
 // with the other half's weight lanes zeroed (lanes with g < 2 carry elements
 // 0 .. 15), each partial scaled by its own d * sc.
 template <int G>
-__global__ void __launch_bounds__(256, 2) stream_down_kq_kernel(ExpertLaunch L)
+struct KqStreamDown {
+static constexpr int NB = 8 * G;                       // 32-element blocks per group
+using QL = WaveRows<16 * NB>;                          // 16 bytes of low nibbles per block
+using QH = WaveRows<8 * NB>;                           // 8 bytes of high parts per block
+static constexpr size_t LDS = kqs::WAVES * 16 * (QL::RS + QH::RS);
+static constexpr int WAVES_PER_SIMD = 4;
+static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int n_blocks, uint8_t *lds)
 {
-    constexpr int NB = 8 * G;                          // 32-element blocks per group
-    using QL = WaveRows<16 * NB>;                      // 16 bytes of low nibbles per block
-    using QH = WaveRows<8 * NB>;                       // 8 bytes of high parts per block
-    __shared__ __attribute__((aligned(16))) uint8_t lst[kqs::WAVES][16 * QL::RS];
-    __shared__ __attribute__((aligned(16))) uint8_t hst[kqs::WAVES][16 * QH::RS];
+    uint8_t (*lst)[16 * QL::RS] = reinterpret_cast<uint8_t (*)[16 * QL::RS]>(lds);
+    uint8_t (*hst)[16 * QH::RS] = reinterpret_cast<uint8_t (*)[16 * QH::RS]>(lds + kqs::WAVES * 16 * QL::RS);
     int t;
     WorkItem it;
-    if (!kq_tile(L, L.d / (kqs::WAVES * kqs::ROWS), t, it) || it.nrows == 0 ||
+    if (!kq_tile(L, L.d / (kqs::WAVES * kqs::ROWS), block, n_blocks, t, it) || it.nrows == 0 ||
         !slot_current(it, L.gen_dev, L.status))      // nrows 0: unpublished expert, no work
         return;
     const int n = it.nrows, d = L.d, I = L.I, nsb = I / 256;
@@ -351,6 +365,14 @@ __global__ void __launch_bounds__(256, 2) stream_down_kq_kernel(ExpertLaunch L)
             y[int64_t(tok) * d] = f32_to_bf16(acc[i] * w);
         }
     }
+}
+};
+
+template <int G>
+__global__ void __launch_bounds__(256, 2) stream_down_kq_kernel(ExpertLaunch L)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[KqStreamDown<G>::LDS];
+    KqStreamDown<G>::run(L, int(blockIdx.x), int(gridDim.x), lds);
 }
 
 namespace {
@@ -507,14 +529,16 @@ __device__ __forceinline__ void unpack_k6_pair(uint32_t lo4, uint32_t hi2, int s
 // elements ahead (two buffers); thread c < TN reads column c's header one
 // super-block ahead and decodes it into the tables.
 template <class S>
-__global__ void __launch_bounds__(S::THREADS, S::WPC *S::WAVES / 4) tile_kq_kernel(ExpertLaunch L)
+struct KqTile {
+static constexpr size_t LDS = S::LDS;
+static constexpr int WAVES_PER_SIMD = S::WPC * S::WAVES / 4;
+static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int n_blocks, uint8_t *lds8)
 {
     using namespace kqt;
     constexpr bool GU = S::GU;
     constexpr int BM = S::BM, TN = S::TN, WAVES = S::WAVES, MB = S::MB, NB = S::NB, STAGE = S::STAGE;
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds8[];
     int n_items, n_tiles;
-    const int t = launch_tile(L, n_items, n_tiles);
+    const int t = launch_tile(L, block, n_blocks, n_items, n_tiles);
     if (t < 0)
         return;                                   // past the device-built list's tiles
     const WorkItem it = L.items[find_item(L.items, n_items, t)];
@@ -849,6 +873,14 @@ __global__ void __launch_bounds__(S::THREADS, S::WPC *S::WAVES / 4) tile_kq_kern
         }
     }
 }
+};
+
+template <class S>
+__global__ void __launch_bounds__(S::THREADS, S::WPC *S::WAVES / 4) tile_kq_kernel(ExpertLaunch L)
+{
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds8[];
+    KqTile<S>::run(L, int(blockIdx.x), int(gridDim.x), lds8);
+}
 
 // Tokens for the k4 tiles: xh[t] = fp16(2^k x[t]) with elements 0 4 1 5 2 6 3 7 of each group of eight, k = xexp[t]
 // putting the row's largest magnitude in [2^9, 2^10) (0 for rows of zeros or with an infinity or NaN; at most
@@ -926,11 +958,28 @@ using KqSmall = kqt::Shape<GU, 64, 128, 4, 3>;
 template <bool GU>
 using KqBig = kqt::Shape<GU, 128, 256, 4, 2>;
 
+// The 64-row gate/up tiles and the stream list in one launch (both_kernel).
+// Measured (MI355X, E 512, d 2048, I 512, K 10, router bias 0.3 ln Zipf(1.5);
+// us): two launches 28 + 83 (128 tokens), 36 + 101 (251), 95 + 121 (1013);
+// together 92, 124, 207.  Down stays in two: the stream kernel runs five
+// workgroups per CU alone, three beside the tiles' LDS (130 against 21 + 88).
+hipError_t launch_gateup_kq_both(const ExpertLaunch &T, const ExpertLaunch &S, hipStream_t s)
+{
+    using Tile = KqTile<KqSmall<true>>;
+    const int nq = S.d / 128;
+    if (nq % 8 == 0)
+        return launch_both<Tile, KqStreamGateUp<8, 2>>(T, S, s);
+    if (nq % 4 == 0)
+        return launch_both<Tile, KqStreamGateUp<4, 2>>(T, S, s);
+    return launch_both<Tile, KqStreamGateUp<2, 2>>(T, S, s);
+}
+
 template <template <bool> class S, int R>
 const KernelSet kq_set{kq_tiles<S<true>>, tiles_gateup_kq_stream<R>, kq_tiles<S<false>>, tiles_down_kq_stream,
                        kq_geom<S<true>>, kq_geom<S<false>>,
                        launch_kq_tile<S<true>>, launch_gateup_kq_stream<R>,
-                       launch_kq_tile<S<false>>, launch_down_kq_stream};
+                       launch_kq_tile<S<false>>, launch_down_kq_stream,
+                       R == 2 && S<true>::BM == 64 ? launch_gateup_kq_both : nullptr};
 
 }  // namespace
 

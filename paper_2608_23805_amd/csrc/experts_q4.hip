@@ -56,16 +56,16 @@ constexpr int WAVES = 4, ROWS = 16;
 
 // Tile t of a stream launch and its item: from the device-built list (the
 // grid is then an upper bound) or the host list.
-__device__ __forceinline__ bool q4_tile(const ExpertLaunch &L, int per_item, int &t, WorkItem &it)
+__device__ __forceinline__ bool q4_tile(const ExpertLaunch &L, int per_item, int b, int n_blocks, int &t, WorkItem &it)
 {
     if (L.direct.demand) {
         int i, local;
-        direct_tile(int(blockIdx.x), per_item, i, local);
+        direct_tile(b, per_item, i, local);
         t = i * per_item + local;
         return direct_item(L.direct, i, per_item, L.status, it);
     }
     int n_items, n_tiles;
-    t = launch_tile(L, n_items, n_tiles);
+    t = launch_tile(L, b, n_blocks, n_items, n_tiles);
     if (t < 0)
         return false;
     it = L.items[find_item(L.items, n_items, t)];
@@ -112,13 +112,16 @@ __device__ __forceinline__ float scale_at(const uint32_t *w, int b)
 // fragment loads, not the codes or the arithmetic, bound the kernel (halving
 // its vector operations alone gained 5%), so launches of many items take R = 2.
 template <int CH, int R>
-__global__ void __launch_bounds__(256, 2) stream_gateup_q4_kernel(ExpertLaunch L)
+struct Q4StreamGateUp {
+using Rows = WaveRows<16 * CH>;
+static constexpr int NM = 2 * R;                       // 16-row groups: R of Wg, then R of Wu
+static constexpr int REGION = NM * 16 * Rows::RS > NM * 1024 ? NM * 16 * Rows::RS : NM * 1024;
+static constexpr size_t LDS = q4s::WAVES * REGION;
+static constexpr int WAVES_PER_SIMD = 3;
+static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int n_blocks, uint8_t *lds)
 {
-    using Rows = WaveRows<16 * CH>;
-    constexpr int NM = 2 * R;                          // 16-row groups: R of Wg, then R of Wu
-    constexpr int REGION = NM * 16 * Rows::RS > NM * 1024 ? NM * 16 * Rows::RS : NM * 1024;
     // a wavefront's rows, then (its own part) its partial sums
-    __shared__ __attribute__((aligned(16))) uint8_t wst[q4s::WAVES][REGION];
+    uint8_t (*wst)[REGION] = reinterpret_cast<uint8_t (*)[REGION]>(lds);
     const int d = L.d, I = L.I, nblk = d / 32, nq = nblk / q4s::WAVES;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
@@ -135,7 +138,7 @@ __global__ void __launch_bounds__(256, 2) stream_gateup_q4_kernel(ExpertLaunch L
     }
     int t;
     WorkItem it;
-    if (!q4_tile(L, I / (q4s::ROWS * R), t, it) || it.nrows == 0)   // nrows 0: unpublished expert, no work
+    if (!q4_tile(L, I / (q4s::ROWS * R), block, n_blocks, t, it) || it.nrows == 0)   // nrows 0: unpublished expert, no work
         return;
     const uint32_t gnow = slot_gen_now(it, L.gen_dev);
     const int n = it.nrows;
@@ -224,6 +227,14 @@ __global__ void __launch_bounds__(256, 2) stream_gateup_q4_kernel(ExpertLaunch L
             if (4 * g + k < n)
                 act[int64_t(4 * g + k) * I + 16 * m] = f32_to_bf16(silu(acc[m][k]) * acc[m + R][k]);
 }
+};
+
+template <int CH, int R>
+__global__ void __launch_bounds__(256, 2) stream_gateup_q4_kernel(ExpertLaunch L)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[Q4StreamGateUp<CH, R>::LDS];
+    Q4StreamGateUp<CH, R>::run(L, int(blockIdx.x), int(gridDim.x), lds);
+}
 
 // Down, 4-bit stream path: a workgroup owns 64 R output columns (16 R per
 // wavefront) over all of I, in chunks of CH blocks whose nibbles (through
@@ -232,13 +243,17 @@ __global__ void __launch_bounds__(256, 2) stream_gateup_q4_kernel(ExpertLaunch L
 // the item's rows repeat its last row), and weights the B operand (outputs:
 // tokens 4g .. 4g + 3 of columns c0 + 16 m + r).
 template <int CH, int R>
-__global__ void __launch_bounds__(256, 2) stream_down_q4_kernel(ExpertLaunch L)
+struct Q4StreamDown {
+using Rows = WaveRows<16 * CH>;
+static constexpr int REGION = R * 16 * Rows::RS;
+static constexpr size_t LDS = q4s::WAVES * REGION;
+static constexpr int WAVES_PER_SIMD = 4;
+static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int n_blocks, uint8_t *lds)
 {
-    using Rows = WaveRows<16 * CH>;
-    __shared__ __attribute__((aligned(16))) uint8_t wst[q4s::WAVES][R * 16 * Rows::RS];
+    uint8_t (*wst)[REGION] = reinterpret_cast<uint8_t (*)[REGION]>(lds);
     int t;
     WorkItem it;
-    if (!q4_tile(L, L.d / (q4s::WAVES * q4s::ROWS * R), t, it) || it.nrows == 0)   // nrows 0: unpublished expert
+    if (!q4_tile(L, L.d / (q4s::WAVES * q4s::ROWS * R), block, n_blocks, t, it) || it.nrows == 0)   // nrows 0: unpublished expert
         return;
     // the generation is read here and compared before the stores, and the row weights are read with the
     // first weights, so nothing waits between the item lookup and the weight loads
@@ -304,6 +319,14 @@ __global__ void __launch_bounds__(256, 2) stream_down_q4_kernel(ExpertLaunch L)
         for (int m = 0; m < R; ++m)
             if (4 * g + k < n)
                 y[int64_t(4 * g + k) * d + 16 * m] = f32_to_bf16(acc[m][k] * rw[k]);
+}
+};
+
+template <int CH, int R>
+__global__ void __launch_bounds__(256, 2) stream_down_q4_kernel(ExpertLaunch L)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[Q4StreamDown<CH, R>::LDS];
+    Q4StreamDown<CH, R>::run(L, int(blockIdx.x), int(gridDim.x), lds);
 }
 
 template <int R>
@@ -380,14 +403,16 @@ struct Shape {
 // one more MFMA per token fragment, against a fragment of -136, and is the C
 // input of that fragment's block partials.
 template <class S>
-__global__ void __launch_bounds__(S::THREADS, S::WPC *S::WAVES / 4) tile_q4_kernel(ExpertLaunch L)
+struct Q4Tile {
+static constexpr size_t LDS = S::LDS;
+static constexpr int WAVES_PER_SIMD = S::WPC * S::WAVES / 4;
+static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int n_blocks, uint8_t *lds8)
 {
     using namespace q4t;
     constexpr bool GU = S::GU;
     constexpr int BM = S::BM, TN = S::TN, WAVES = S::WAVES, MB = S::MB, NB = S::NB, STAGE = S::STAGE;
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds8[];
     int n_items, n_tiles;
-    const int t = launch_tile(L, n_items, n_tiles);
+    const int t = launch_tile(L, block, n_blocks, n_items, n_tiles);
     if (t < 0)
         return;                                   // past the device-built list's tiles
     const WorkItem it = L.items[find_item(L.items, n_items, t)];
@@ -561,6 +586,14 @@ __global__ void __launch_bounds__(S::THREADS, S::WPC *S::WAVES / 4) tile_q4_kern
         }
     }
 }
+};
+
+template <class S>
+__global__ void __launch_bounds__(S::THREADS, S::WPC *S::WAVES / 4) tile_q4_kernel(ExpertLaunch L)
+{
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds8[];
+    Q4Tile<S>::run(L, int(blockIdx.x), int(gridDim.x), lds8);
+}
 
 template <class S>
 static int q4_tiles(int nrows, int d, int I)
@@ -587,11 +620,38 @@ using Q4GateSmall = q4t::Shape<true, 64, 128, 1, 4, 4>;
 using Q4GateBig = q4t::Shape<true, 128, 128, 2, 2, 2>;
 using Q4Down = q4t::Shape<false, 64, 128, 1, 2, 6>;
 
+// The 64-row gate/up tiles, or the down tiles, and the stream list in one
+// launch (both_kernel).  Measured (MI355X, E 512, d 2048, I 512, K 10, router
+// bias 0.3 ln Zipf(1.5); gate/up, us): two launches 23.5 + 74 (128 tokens),
+// 44 + 107 (509), 95 + 112 (1013); together 83, 147, 196; down 11.5 + 46,
+// 24 + 66, 49 + 69 and 50, 87, 114.  The down tiles take four workgroups per
+// CU here, not six, which is what the stream list's registers allow.
+using Q4DownBoth = q4t::Shape<false, 64, 128, 1, 4, 4>;
+
+static hipError_t launch_gateup_q4_both(const ExpertLaunch &T, const ExpertLaunch &S, hipStream_t s)
+{
+    const int nq = S.d / 128;
+    if (nq % 8 == 0)
+        return launch_both<Q4Tile<Q4GateSmall>, Q4StreamGateUp<8, 2>>(T, S, s);
+    if (nq % 4 == 0)
+        return launch_both<Q4Tile<Q4GateSmall>, Q4StreamGateUp<4, 2>>(T, S, s);
+    return launch_both<Q4Tile<Q4GateSmall>, Q4StreamGateUp<2, 2>>(T, S, s);
+}
+
+static hipError_t launch_down_q4_both(const ExpertLaunch &T, const ExpertLaunch &S, hipStream_t s)
+{
+    if (S.I % 256 == 0)
+        return launch_both<Q4Tile<Q4DownBoth>, Q4StreamDown<8, 2>>(T, S, s);
+    return launch_both<Q4Tile<Q4DownBoth>, Q4StreamDown<4, 2>>(T, S, s);
+}
+
 template <class G, int R>
 static const KernelSet q4_set{q4_tiles<G>, tiles_gateup_q4_stream<R>, q4_tiles<Q4Down>, tiles_down_q4_stream<R>,
                               q4_geom<G>, q4_geom<Q4Down>,
                               launch_q4_tile<G>, launch_gateup_q4_stream<R>,
-                              launch_q4_tile<Q4Down>, launch_down_q4_stream<R>};
+                              launch_q4_tile<Q4Down>, launch_down_q4_stream<R>,
+                              R == 2 && G::BM == 64 ? launch_gateup_q4_both : nullptr,
+                              R == 2 && G::BM == 64 ? launch_down_q4_both : nullptr};
 
 // Tile forms by the mean rows per expert, R of the stream kernels by the
 // routed rows, which bound the launch's items: from 32 on its workgroups fill

@@ -40,17 +40,24 @@ struct MidShape {
     static_assert(LDS * WPC <= 160 * 1024 && LPS * (NBUF - 2) < 64, "");
 };
 
+// The 64-row shape, alone and beside the stream list (less LDS there, so that three workgroups share a CU as the
+// stream kernels' do).
+using Mid64 = MidShape<64, 128, 1, 4, 3, 2>;
+using Mid64Both = MidShape<64, 128, 1, 4, 2, 3>;
+
 template <RingMode MODE, class S>
-__global__ void __launch_bounds__(S::THREADS, S::WPC * S::WAVES / 4) mid_gemm_kernel(ExpertLaunch L)
+struct MidTile {
+static constexpr size_t LDS = S::LDS;
+static constexpr int WAVES_PER_SIMD = S::WPC * S::WAVES / 4;
+static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int n_blocks, uint8_t *lds8)
 {
     constexpr int BM = S::BM, TN = S::TN, NBUF = S::NBUF, WAVES = S::WAVES, BK = S::BK, ROWB = S::ROWB,
                   STAGE = S::STAGE, MB = S::MB, NB = S::NB, LA = S::LA, LB = S::LB, LPS = S::LPS;
     constexpr bool GU = MODE == RingMode::GateUp;
     constexpr bool RT = MODE == RingMode::Router;
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds8[];
 
     int n_items = 1, n_tiles = 0;
-    const int t = RT ? xcd_swizzle(int(blockIdx.x), int(gridDim.x)) : launch_tile(L, n_items, n_tiles);
+    const int t = RT ? xcd_swizzle(block, n_blocks) : launch_tile(L, block, n_blocks, n_items, n_tiles);
     if (t < 0)
         return;                                   // past the device-built list's tiles
     const WorkItem it = RT ? WorkItem{-1, -1, 0u, 0, L.T, 0} : L.items[find_item(L.items, n_items, t)];
@@ -236,6 +243,14 @@ __global__ void __launch_bounds__(S::THREADS, S::WPC * S::WAVES / 4) mid_gemm_ke
             }
         }
     }
+}
+};
+
+template <RingMode MODE, class S>
+__global__ void __launch_bounds__(S::THREADS, S::WPC * S::WAVES / 4) mid_gemm_kernel(ExpertLaunch L)
+{
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds8[];
+    MidTile<MODE, S>::run(L, int(blockIdx.x), int(gridDim.x), lds8);
 }
 
 }  // namespace msi

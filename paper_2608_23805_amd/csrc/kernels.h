@@ -124,16 +124,56 @@ struct ExpertLaunch {
 // list (L.dev_n; the grid is an upper bound, tiles spread over the XCDs by
 // the real count) or the host list (the grid is the tile count); -1 if this
 // workgroup has no tile.  (Scalar loads: the counts are uniform.)
-__device__ __forceinline__ int launch_tile(const ExpertLaunch &L, int &n_items, int &n_tiles)
+__device__ __forceinline__ int launch_tile(const ExpertLaunch &L, int b, int n_blocks, int &n_items, int &n_tiles)
 {
     if (L.dev_n) {
         n_items = __builtin_amdgcn_readfirstlane(L.dev_n->n_items);
         n_tiles = __builtin_amdgcn_readfirstlane(L.dev_n->n_tiles);
-        return xcd_tile(int(blockIdx.x), n_tiles);
+        return xcd_tile(b, n_tiles);
     }
     n_items = L.n_items;
     n_tiles = L.n_tiles;
-    return xcd_swizzle(int(blockIdx.x), int(gridDim.x));
+    return xcd_swizzle(b, n_blocks);
+}
+__device__ __forceinline__ int launch_tile(const ExpertLaunch &L, int &n_items, int &n_tiles)
+{
+    return launch_tile(L, int(blockIdx.x), int(gridDim.x), n_items, n_tiles);
+}
+
+// The tile-path and the stream-path list of a forward in one launch: the first
+// tile_blocks workgroups (a multiple of 8, so both lists keep their XCDs) are
+// the tile list's.  Few tiles (the shared expert's and those of the busiest
+// experts of a small batch) reach few CUs and last as long as a tile does; run
+// beside the stream list they cost little, and a launch and its drain go.
+// Tile and Stream: run(L, block, blocks, lds), 256 threads, LDS bytes.  Only
+// for device-built lists, whose grids bound the tiles instead of counting them.
+template <class Tile, class Stream>
+__global__ void __launch_bounds__(256, Tile::WAVES_PER_SIMD < Stream::WAVES_PER_SIMD ? Tile::WAVES_PER_SIMD
+                                                                                     : Stream::WAVES_PER_SIMD)
+    both_kernel(ExpertLaunch T, ExpertLaunch S, int tile_blocks)
+{
+    extern __shared__ __attribute__((aligned(1024))) uint8_t both_lds[];
+    const int b = int(blockIdx.x);
+    if (b < tile_blocks)
+        Tile::run(T, b, tile_blocks, both_lds);
+    else
+        Stream::run(S, b - tile_blocks, int(gridDim.x) - tile_blocks, both_lds);
+}
+
+template <class Tile, class Stream>
+inline hipError_t launch_both(const ExpertLaunch &T, const ExpertLaunch &S, hipStream_t s)
+{
+    constexpr size_t LDS = Tile::LDS > Stream::LDS ? Tile::LDS : Stream::LDS;
+    if (!T.dev_n || !S.dev_n || T.n_tiles % 8 != 0)
+        return hipErrorInvalidValue;
+    static_assert(LDS <= 80 * 1024, "");
+    if constexpr (LDS > 64 * 1024) {
+        static const hipError_t e = allow_large_lds(reinterpret_cast<const void *>(&both_kernel<Tile, Stream>));
+        if (e != hipSuccess)
+            return e;
+    }
+    launch_k(both_kernel<Tile, Stream>, T.n_tiles + S.n_tiles, 256, LDS, s, T, S, T.n_tiles);
+    return hipGetLastError();
 }
 
 // Row and weight-slice geometry of a tile-path launch kind: an item of n
@@ -174,6 +214,7 @@ hipError_t launch_gateup_tile(const ExpertLaunch &L, hipStream_t s);
 hipError_t launch_down_tile(const ExpertLaunch &L, hipStream_t s);
 hipError_t launch_gateup_stream(const ExpertLaunch &L, hipStream_t s);
 hipError_t launch_down_stream(const ExpertLaunch &L, hipStream_t s);
+hipError_t launch_gateup_both(const ExpertLaunch &T, const ExpertLaunch &S, hipStream_t s);
 hipError_t launch_gateup_f32(const ExpertLaunch &L, hipStream_t s);
 hipError_t launch_down_f32(const ExpertLaunch &L, hipStream_t s);
 
@@ -196,6 +237,9 @@ struct KernelSet {
     Tiles tiles_gu_tile, tiles_gu_stream, tiles_dn_tile, tiles_dn_stream;
     Geom geom_gu, geom_dn;
     Launch gu_tile, gu_stream, dn_tile, dn_stream;
+    // tile and stream list of a device-built pair in one launch, or null
+    using Both = hipError_t (*)(const ExpertLaunch &tile, const ExpertLaunch &stream, hipStream_t s);
+    Both gu_both = nullptr, dn_both = nullptr;
 };
 // kernels of a batch of `rows` routed rows (T * K) over E experts
 const KernelSet &q4_kernels(uint64_t rows, uint64_t E);

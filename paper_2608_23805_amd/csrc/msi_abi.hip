@@ -1190,10 +1190,18 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
         DS.items = W.items[3];
         DS.dev_n = p->dcount_dev + 3;
         DS.n_tiles = round8(int64_t(n_stream_max) * W.per_dn_stream);
-        HIP_OK(p->timed_launch(MSI_K_GATEUP_TILE, cs, [&] { return ks.gu_tile(GT, cs); }));
-        HIP_OK(p->timed_launch(MSI_K_GATEUP_STREAM, cs, [&] { return ks.gu_stream(GS, cs); }));
-        HIP_OK(p->timed_launch(MSI_K_DOWN_TILE, cs, [&] { return ks.dn_tile(DT, cs); }));
-        HIP_OK(p->timed_launch(MSI_K_DOWN_STREAM, cs, [&] { return ks.dn_stream(DS, cs); }));
+        if (ks.gu_both) {
+            HIP_OK(p->timed_launch(MSI_K_GATEUP_STREAM, cs, [&] { return ks.gu_both(GT, GS, cs); }));
+        } else {
+            HIP_OK(p->timed_launch(MSI_K_GATEUP_TILE, cs, [&] { return ks.gu_tile(GT, cs); }));
+            HIP_OK(p->timed_launch(MSI_K_GATEUP_STREAM, cs, [&] { return ks.gu_stream(GS, cs); }));
+        }
+        if (ks.dn_both) {
+            HIP_OK(p->timed_launch(MSI_K_DOWN_STREAM, cs, [&] { return ks.dn_both(DT, DS, cs); }));
+        } else {
+            HIP_OK(p->timed_launch(MSI_K_DOWN_TILE, cs, [&] { return ks.dn_tile(DT, cs); }));
+            HIP_OK(p->timed_launch(MSI_K_DOWN_STREAM, cs, [&] { return ks.dn_stream(DS, cs); }));
+        }
         // large grid: no arrival counter (the next forward clears the status word)
         const CombinePublish pub{p->status_dev, nullptr, p->tail_hdev, a->r.demand};
         HIP_OK(p->timed_launch(MSI_K_COMBINE, cs, [&] {

@@ -34,7 +34,6 @@ TileGeom geom_down_tile(int d, int I)
 
 // Shapes of the tile path for few rows per expert (kernel_set holds the rule between them and the 256-row
 // form), and of the router logits.
-using Mid64 = MidShape<64, 128, 1, 4, 3, 2>;
 using Mid128 = MidShape<128, 256, 2, 4, 3, 1>;
 using Router32 = MidShape<32, 32, 2, 2, 6, 1>;
 using Router64 = MidShape<64, 64, 2, 2, 4, 2>;
@@ -76,7 +75,8 @@ template <class S>
 static const KernelSet mid_set{tiles_gateup_mid<S>, tiles_gateup_stream, tiles_down_mid<S>, tiles_down_stream,
                                geom_gateup_mid<S>, geom_down_mid<S>,
                                launch_mid<RingMode::GateUp, S>, launch_gateup_stream,
-                               launch_mid<RingMode::Down, S>, launch_down_stream};
+                               launch_mid<RingMode::Down, S>, launch_down_stream,
+                               S::BM == Mid64Both::BM ? launch_gateup_both : nullptr};
 
 // The tile path's form by the mean rows per expert.  The three are
 // bit-identical, so the choice is the launch's and no result depends on it.
