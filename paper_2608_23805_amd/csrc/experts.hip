@@ -259,8 +259,14 @@ __global__ void __launch_bounds__(256, 3) stream_gateup_kernel(ExpertLaunch L)
 // operand) read row j of the item's act rows straight from memory with each
 // weight batch (the rows are contiguous and few; lanes past the item's rows
 // read its last row, whose outputs are never stored), so no workgroup
-// barrier or LDS staging comes before the first MFMA.
-template <int NB>
+// barrier or LDS staging comes before the first MFMA.  STAGE: the workgroup
+// stages the item's rows in LDS once instead.  The four wavefronts read the
+// same rows, and a direct load of 16 of them touches 16 lines for the 8 of a
+// weight load; with ten rows and more that costs more than the barrier.
+// Measured (MI355X, E 512, d 2048, I 512, K 10; direct / staged, us): 2.5 mean
+// rows 141 / 144, 5 161 / 162, 6 167 / 166, 8 178 / 169, 10 186 / 170, 16
+// (half of the experts) 129 / 113; I 768, E 128: 8 rows 34 / 35, 12 35 / 33.
+template <int NB, bool STAGE>
 struct StreamDown {
 static constexpr int U = 4, SL = U / 2;
 static constexpr int REGION = SL * slab::BYTES;
@@ -294,12 +300,27 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
             dst[s][0] = load_stream16(gp0 + k0 + 64 * s);
             dst[s][1] = load_stream16(gp1 + k0 + 64 * s);
         }
+        if constexpr (!STAGE)
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            adst[u] = *reinterpret_cast<const u32x4 *>(ap + k0 + 32 * u);
+            for (int u = 0; u < U; ++u)
+                adst[u] = *reinterpret_cast<const u32x4 *>(ap + k0 + 32 * u);
     };
     u32x4 w[2][SL][2], av[2][U];
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    // staged rows: thread t brings 16-byte piece t % 16 of every 128 columns of row t / 16; the row stride
+    // sends the 16 rows' pieces of a fragment read to different banks
+    const int sr = 2 * I + 16;
+    uint8_t *srow = lds + stream::WAVES * REGION + (threadIdx.x >> 4) * sr + 16 * (threadIdx.x & 15);
+    const uint8_t *sfrag = lds + stream::WAVES * REGION + j * sr + 2 * kg;
+    const uint16_t *grow = reinterpret_cast<const uint16_t *>(sh ? L.act_s : L.act) +
+                           int64_t(it.row0 + min(int(threadIdx.x >> 4), n - 1)) * I + 8 * (threadIdx.x & 15);
+    constexpr int NS = 4;                             // pieces loaded ahead of the first weights: 512 columns
+    u32x4 sv[NS];
+    if constexpr (STAGE)
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+            if (128 * i < I)
+                sv[i] = *reinterpret_cast<const u32x4 *>(grow + 128 * i);
     const int nchunk = I / (32 * U * NB);
     for (int c = 0; c < nchunk; ++c) {
         const int kc = c * 32 * U * NB;
@@ -307,6 +328,15 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
         load_w(w[0], av[0], kc);
         if (NB > 1)
             load_w(w[1], av[1], kc + 32 * U);
+        if (STAGE && c == 0) {
+#pragma unroll
+            for (int i = 0; i < NS; ++i)
+                if (128 * i < I)
+                    *reinterpret_cast<u32x4 *>(srow + 256 * i) = sv[i];
+            for (int i = NS; 128 * i < I; ++i)
+                *reinterpret_cast<u32x4 *>(srow + 256 * i) = *reinterpret_cast<const u32x4 *>(grow + 128 * i);
+            __syncthreads();
+        }
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             if (b >= 1 && b + 1 < NB)                 // batches 0 and 1 went out with the chunk
@@ -320,7 +350,9 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const u32x4 fw = *reinterpret_cast<const u32x4 *>(t + (u >> 1) * slab::BYTES + slab::frag(lane, u & 1));
-                acc = mfma16(as_bf16x8(fw), as_bf16x8(av[b & 1][u]), acc);
+                const u32x4 fa = STAGE ? *reinterpret_cast<const u32x4 *>(sfrag + 2 * (kc + 32 * (b * U + u)))
+                                       : av[b & 1][u];
+                acc = mfma16(as_bf16x8(fw), as_bf16x8(fa), acc);
             }
             lds_wait();                               // the next batch overwrites this wavefront's slabs
         }
@@ -336,11 +368,11 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
 }
 };
 
-template <int NB>
+template <int NB, bool STAGE>
 __global__ void __launch_bounds__(256, 4) stream_down_kernel(ExpertLaunch L)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[StreamDown<NB>::LDS];
-    StreamDown<NB>::run(L, int(blockIdx.x), int(gridDim.x), lds);
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    StreamDown<NB, STAGE>::run(L, int(blockIdx.x), int(gridDim.x), lds);
 }
 
 hipError_t launch_gateup_stream(const ExpertLaunch &L, hipStream_t s)
@@ -360,18 +392,29 @@ hipError_t launch_gateup_stream(const ExpertLaunch &L, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_down_stream(const ExpertLaunch &L, hipStream_t s)
+template <bool STAGE>
+static hipError_t launch_down(const ExpertLaunch &L, hipStream_t s)
 {
-    if (L.n_tiles == 0)
-        return hipSuccess;
+    const int lds = int(StreamDown<1, STAGE>::LDS) + (STAGE ? 16 * (2 * L.I + 16) : 0);
     // chunks of NB batches of 128 columns must divide I (I % 128 == 0)
     if (L.I % 512 == 0)
-        launch_k(stream_down_kernel<4>, L.n_tiles, 256, 0, s, L);
+        launch_k(stream_down_kernel<4, STAGE>, L.n_tiles, 256, lds, s, L);
     else if (L.I % 256 == 0)
-        launch_k(stream_down_kernel<2>, L.n_tiles, 256, 0, s, L);
+        launch_k(stream_down_kernel<2, STAGE>, L.n_tiles, 256, lds, s, L);
     else
-        launch_k(stream_down_kernel<1>, L.n_tiles, 256, 0, s, L);
+        launch_k(stream_down_kernel<1, STAGE>, L.n_tiles, 256, lds, s, L);
     return hipGetLastError();
+}
+
+hipError_t launch_down_stream(const ExpertLaunch &L, hipStream_t s)
+{
+    return L.n_tiles == 0 ? hipSuccess : launch_down<false>(L, s);
+}
+
+// staged where the rows leave a CU its four workgroups: 8 KB of weights and 32 I + 256 bytes in 40 KB
+hipError_t launch_down_stream_staged(const ExpertLaunch &L, hipStream_t s)
+{
+    return L.n_tiles == 0 ? hipSuccess : L.I <= 896 ? launch_down<true>(L, s) : launch_down<false>(L, s);
 }
 
 // The 64-row tiles and the stream list in one launch (both_kernel).  Measured
@@ -499,16 +542,7 @@ namespace msi {
 
 hipError_t init_kernel_attributes()
 {
-    hipError_t e = hipSuccess;
-    auto set = [&](const void *f) {
-        if (e == hipSuccess)
-            e = allow_large_lds(f);
-    };
-    set(reinterpret_cast<const void *>(&stream_down_kernel<4>));
-    set(reinterpret_cast<const void *>(&stream_down_kernel<2>));
-    set(reinterpret_cast<const void *>(&stream_down_kernel<1>));
-    if (e == hipSuccess)
-        e = init_tile_attributes();
+    hipError_t e = init_tile_attributes();
     if (e == hipSuccess)
         e = init_route_attributes();
     if (e == hipSuccess)

@@ -214,6 +214,7 @@ hipError_t launch_gateup_tile(const ExpertLaunch &L, hipStream_t s);
 hipError_t launch_down_tile(const ExpertLaunch &L, hipStream_t s);
 hipError_t launch_gateup_stream(const ExpertLaunch &L, hipStream_t s);
 hipError_t launch_down_stream(const ExpertLaunch &L, hipStream_t s);
+hipError_t launch_down_stream_staged(const ExpertLaunch &L, hipStream_t s);
 hipError_t launch_gateup_both(const ExpertLaunch &T, const ExpertLaunch &S, hipStream_t s);
 hipError_t launch_gateup_f32(const ExpertLaunch &L, hipStream_t s);
 hipError_t launch_down_f32(const ExpertLaunch &L, hipStream_t s);

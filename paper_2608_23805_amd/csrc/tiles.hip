@@ -71,11 +71,12 @@ static hipError_t launch_mid(const ExpertLaunch &L, hipStream_t s)
     return hipGetLastError();
 }
 
-template <class S>
+template <class S, bool STAGE>
 static const KernelSet mid_set{tiles_gateup_mid<S>, tiles_gateup_stream, tiles_down_mid<S>, tiles_down_stream,
                                geom_gateup_mid<S>, geom_down_mid<S>,
                                launch_mid<RingMode::GateUp, S>, launch_gateup_stream,
-                               launch_mid<RingMode::Down, S>, launch_down_stream,
+                               launch_mid<RingMode::Down, S>,
+                               STAGE ? launch_down_stream_staged : launch_down_stream,
                                S::BM == Mid64Both::BM ? launch_gateup_both : nullptr};
 
 // The tile path's form by the mean rows per expert.  The three are
@@ -88,12 +89,16 @@ static const KernelSet mid_set{tiles_gateup_mid<S>, tiles_gateup_stream, tiles_d
 //     160       692+420  591+382   533+348
 // (below 64 rows the 64-row form streams the weights with two workgroups per
 // CU; past it most experts need two of its tiles, each reading the weights.)
+// Past 8 mean rows the stream list's down stages its act rows (both sides are
+// at its kernel).
 const KernelSet &bf16_kernels(uint64_t rows, uint64_t E)
 {
     static const KernelSet ring256{tiles_gateup_tile, tiles_gateup_stream, tiles_down_tile, tiles_down_stream,
                                    geom_gateup_tile, geom_down_tile,
-                                   launch_gateup_tile, launch_gateup_stream, launch_down_tile, launch_down_stream};
-    return rows <= 48 * E ? mid_set<Mid64> : rows <= 112 * E ? mid_set<Mid128> : ring256;
+                                   launch_gateup_tile, launch_gateup_stream, launch_down_tile, launch_down_stream_staged};
+    if (rows <= 48 * E)
+        return rows <= 8 * E ? mid_set<Mid64, false> : mid_set<Mid64, true>;
+    return rows <= 112 * E ? mid_set<Mid128, true> : ring256;
 }
 
 // workgroups of a persistent launch: one per compute unit
