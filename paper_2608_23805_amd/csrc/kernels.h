@@ -70,7 +70,8 @@ struct RouteOut {
     float *row_weight;
 };
 // top-K + restricted softmax + permutation of logits L (bias included): one
-// fused workgroup when T <= 256, else top-K, histogram, scan and scatter
+// fused workgroup when T <= 16, else top-K over all CUs and the permutation (one
+// workgroup up to 512 tokens; histogram, scan and scatter above)
 hipError_t launch_route_select(const float *L, const RouteOut &o, int32_t *blockhist, int T, int K, int E,
                                hipStream_t s);
 hipError_t init_route_attributes();

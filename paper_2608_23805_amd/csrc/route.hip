@@ -441,6 +441,88 @@ __global__ void __launch_bounds__(1024) route_small_kernel(const float *__restri
     route_small_body<PER, PERM_BLOCK>(bits, L, select, o, T, K, E);
 }
 
+// The permutation of PERM_BLOCK + 1 .. PERM_ONE_MAX tokens by one workgroup, from the
+// selection of a launch before it: a bitmask of ceil(T / 32) words per expert
+// (an odd stride, so experts' words differ in bank), its words' running
+// counts, and one scan over the experts; rows of an expert are its tokens
+// ascending, as in the block kernels.  A thread holds its pairs' experts and
+// weights in registers, all loaded at once.  Latency-bound; measured with the
+// selection's launch (MI355X, E 512, K 10; the three block launches / this
+// one, us): T 257 19.6 / 11.7, 384 20.3 / 13.0, 509 20.4 / 15.0, 768 20.4 /
+// 18.7, 1013 21.6 / 22.4; E 64, K 4: T 400 18.6 / 9.1.  Up to 512 tokens the
+// table of 1024 experts (102 KB) always fits.
+constexpr int PERM_ONE_MAX = 512;
+
+static size_t perm_one_lds(int T, int E)
+{
+    return size_t(E) * (((T + 31) / 32) | 1) * 6;
+}
+
+__global__ void __launch_bounds__(1024) perm_one_kernel(RouteOut o, int T, int K, int E)
+{
+    extern __shared__ uint32_t bits[];          // [E][W | 1], then the running counts, 16 bits each
+    __shared__ int32_t excl[1024];              // first permuted row of each expert
+    __shared__ int32_t wsum[16];
+    constexpr int PAIRS = PERM_ONE_MAX * 16 / 1024;
+    const int W = (T + 31) >> 5, WS = W | 1, n = T * K;
+    uint16_t *below = reinterpret_cast<uint16_t *>(bits + E * WS);
+    int32_t se[PAIRS];
+    float sw[PAIRS];
+#pragma unroll
+    for (int i = 0; i < PAIRS; ++i) {
+        const int a = i * 1024 + int(threadIdx.x);
+        if (a < n) {
+            se[i] = o.idx[a];
+            sw[i] = o.w[a];
+        }
+    }
+    for (int i = threadIdx.x; i < E * WS; i += 1024)
+        bits[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PAIRS; ++i) {
+        const int a = i * 1024 + int(threadIdx.x);
+        if (a < n) {
+            const int t = a / K;
+            atomicOr(&bits[se[i] * WS + (t >> 5)], 1u << (t & 31));
+        }
+    }
+    __syncthreads();
+    const int e = threadIdx.x;
+    int c = 0;
+    if (e < E)
+        for (int q = 0; q < W; ++q) {
+            below[e * WS + q] = uint16_t(c);
+            c += __popc(bits[e * WS + q]);
+        }
+    // one scan of (demanded << 16) + count: T * K <= 8192 keeps the halves apart
+    const int packed = block_scan_incl_1024(c | (c > 0 ? 0x10000 : 0), wsum);
+    const int incl = packed & 0xFFFF, nz = packed >> 16;
+    excl[e] = incl - c;
+    if (e < E) {
+        o.counts[e] = c;
+        o.offsets[e] = incl - c;
+        if (c > 0)
+            o.demand[nz] = e;                   // demanded experts, ascending, after the count
+    }
+    if (e == E - 1) {
+        o.offsets[E] = incl;
+        o.demand[0] = nz;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PAIRS; ++i) {
+        const int a = i * 1024 + int(threadIdx.x);
+        if (a < n) {
+            const int t = a / K, w = se[i] * WS + (t >> 5);
+            const int r = excl[se[i]] + below[w] + __popc(bits[w] & ((1u << (t & 31)) - 1u));
+            o.perm[r] = t;
+            o.inv[a] = r;
+            o.row_weight[r] = sw[i];
+        }
+    }
+}
+
 // ---------------------------------------------------------------- decode routing, bf16, T <= 16
 // Logits, selection and permutation in one launch.  Workgroup g (16
 // wavefronts) streams router rows 16 g .. 16 g + 15: its wavefronts take
@@ -586,6 +668,7 @@ hipError_t init_route_attributes()
     set(reinterpret_cast<const void *>(&route_small_kernel<4>));
     set(reinterpret_cast<const void *>(&route_small_kernel<8>));
     set(reinterpret_cast<const void *>(&route_small_kernel<16>));
+    set(reinterpret_cast<const void *>(&perm_one_kernel));
     set(reinterpret_cast<const void *>(&route_decode_kernel<2, true>));
     set(reinterpret_cast<const void *>(&route_decode_kernel<4, true>));
     set(reinterpret_cast<const void *>(&route_decode_kernel<8, true>));
@@ -671,6 +754,10 @@ hipError_t launch_route_select(const float *L, const RouteOut &o, int32_t *block
         launch_k(topk_kernel<8>, grid, block, 0, s, L, o.idx, o.w, T, E, K);
     else
         launch_k(topk_kernel<16>, grid, block, 0, s, L, o.idx, o.w, T, E, K);
+    if (T <= PERM_ONE_MAX) {
+        launch_k(perm_one_kernel, 1, 1024, perm_one_lds(T, E), s, o, T, K, E);
+        return hipGetLastError();
+    }
     const size_t lds = size_t(E) * (PERM_BLOCK / 32) * sizeof(uint32_t);
     const int nblk = (T + PERM_BLOCK - 1) / PERM_BLOCK;
     launch_k(perm_hist_kernel, nblk, 1024, lds, s, o.idx, blockhist, T, K, E);
