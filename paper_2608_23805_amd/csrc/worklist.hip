@@ -31,7 +31,9 @@ __device__ __forceinline__ int scan_excl_1024(int v, int32_t *wsum, int &total)
 // geom.slices tiles), one with 1..thr rows to the stream lists; ascending by
 // expert, the shared expert's item first in the tile lists, so the lists and
 // their tile numbering are those the host schedule builds for an all-resident
-// round.  A demanded expert without a published slot raises STATUS_MISS.
+// round.  A demanded expert without a published slot raises STATUS_MISS and
+// is in no list: the kernels read slot -1 as the shared expert, whose buffers
+// have T rows and not the T * K its permuted rows go up to.
 // With clear_status the kernel first zeroes the status word (in place of a
 // launch of its own): the store completes before the workgroup's barrier,
 // ahead of any bit this forward raises.
@@ -45,12 +47,14 @@ __global__ void __launch_bounds__(1024) build_worklist_kernel(WorklistArgs A)
     }
     const int e = threadIdx.x;
     const bool in = e < A.E;
-    const int c = in ? A.counts[e] : 0;
     const int slot = in ? A.slot_of[e] : -1;
     const uint32_t gen = in ? A.gen_of[e] : 0u;
     const int row0 = in ? A.offsets[e] : 0;
-    if (c > 0 && slot < 0)
+    int c = in ? A.counts[e] : 0;
+    if (c > 0 && slot < 0) {
         atomicOr(A.status, STATUS_MISS);
+        c = 0;
+    }
     const bool tile = c > A.thr, stream = c > 0 && c <= A.thr;
     const int tg = tile ? (c + A.gu.rows - 1) / A.gu.rows * A.gu.slices : 0;
     const int td = tile ? (c + A.dn.rows - 1) / A.dn.rows * A.dn.slices : 0;
