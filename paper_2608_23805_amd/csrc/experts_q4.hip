@@ -8,9 +8,8 @@
 //
 //  * stream path (<= 16 tokens per expert): tokens as the A operand and
 //    weights as the B operand, tokens read straight from memory and the
-//    nibbles through row-contiguous loads rearranged in LDS (WaveRows); both
-//    operands in pair order (common.h), the codes as the exact bf16 136 + q,
-//    whose offset leaves through the C input as on the tile path.
+//    nibbles through row-contiguous loads rearranged in LDS (WaveRows); the
+//    codes unpacked to exact bf16 q / 16 (C = 0).
 //  * tile path: 64 or 128 tokens x 128 weight rows per workgroup; token rows,
 //    packed nibbles and scales copied from memory straight into two LDS stage
 //    buffers; the codes enter the MFMA as the exact bf16 136 + q, and the
@@ -43,6 +42,24 @@ __device__ __forceinline__ bf16x8 unpack_q4_136(uint32_t w)
     r[1] = __builtin_amdgcn_perm(0x43434343u, lo, 0x04030402u);
     r[2] = __builtin_amdgcn_perm(0x43434343u, hi, 0x04010400u);
     r[3] = __builtin_amdgcn_perm(0x43434343u, hi, 0x04030402u);
+    return __builtin_bit_cast(bf16x8, r);
+}
+
+// 8 nibbles (element e at bits 4e..4e+3, two's complement q) -> 8 exact bf16
+// values q / 16: the 4-bit integer conversion reads the low nibble of a byte
+// and returns q / 16 in binary32, whose top half holds it; thirteen operations
+// per 8 values.
+__device__ __forceinline__ bf16x8 unpack_q4_16th(uint32_t w)
+{
+    uint32_t o = w >> 4;
+    asm("" : "+v"(o));          // (one shift; the conversions then pick their byte of it)
+    u32x4 r;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const float fe = __builtin_amdgcn_cvt_off_f32_i4(int((w >> (8 * h)) & 0xFFu));   // element 2h
+        const float fo = __builtin_amdgcn_cvt_off_f32_i4(int((o >> (8 * h)) & 0xFFu));   // element 2h + 1
+        r[h] = __builtin_amdgcn_perm(__float_as_uint(fo), __float_as_uint(fe), 0x07060302u);
+    }
     return __builtin_bit_cast(bf16x8, r);
 }
 
@@ -107,7 +124,8 @@ __device__ __forceinline__ float scale_at(const uint32_t *w, int b)
 // straight from global memory (lanes past the item's rows repeat its last
 // row and are not stored); the nibbles go through WaveRows (row-contiguous
 // 16-byte loads, rearranged in the wavefront's own LDS region).  Blocks go
-// in chunks of CH, each chunk's loads issued before its first MFMA.  A token
+// in chunks of CH, each chunk's loads issued before its first MFMA.  The sums
+// are sixteenths (exact: a power of two) until they are whole.  A token
 // fragment is 1 KiB from 16 rows and R = 1 gives it to 512 bytes of codes: the
 // fragment loads, not the codes or the arithmetic, bound the kernel (halving
 // its vector operations alone gained 5%), so launches of many items take R = 2.
@@ -173,7 +191,6 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
         for (int m = 0; m < NM; ++m)
             load_scales<CH>(sc[m], sp[m] + c0);
     };
-    const bf16x8 neg136 = __builtin_bit_cast(bf16x8, u32x4{0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u});
     f32x4 acc[NM];
 #pragma unroll
     for (int m = 0; m < NM; ++m)
@@ -186,12 +203,11 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
         const uint8_t *q = wst[wave] + r * Rows::RS + 4 * g;
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-            const bf16x8 xb = pair_order(xv[u]);
-            const f32x4 corr = mfma16(xb, neg136, f32x4{0.f, 0.f, 0.f, 0.f});
+            const bf16x8 xb = as_bf16x8(xv[u]);
 #pragma unroll
             for (int m = 0; m < NM; ++m) {
                 const uint32_t w = *reinterpret_cast<const uint32_t *>(q + m * 16 * Rows::RS + 16 * u);
-                const f32x4 part = mfma16(xb, unpack_u4_pairs(w ^ 0x88888888u), corr);
+                const f32x4 part = mfma16(xb, unpack_q4_16th(w), f32x4{0.f, 0.f, 0.f, 0.f});
                 const float s = scale_at(sc[m], u);
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
@@ -225,7 +241,8 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
 #pragma unroll
         for (int m = 0; m < R; ++m)
             if (4 * g + k < n)
-                act[int64_t(4 * g + k) * I + 16 * m] = f32_to_bf16(silu(acc[m][k]) * acc[m + R][k]);
+                act[int64_t(4 * g + k) * I + 16 * m] =
+                    f32_to_bf16(silu(16.0f * acc[m][k]) * (16.0f * acc[m + R][k]));
 }
 };
 
@@ -272,7 +289,6 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
     Rows wr[R];
     u32x4 av[CH];
     uint32_t sc[R][CH / 2];
-    const bf16x8 neg136 = __builtin_bit_cast(bf16x8, u32x4{0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u});
     f32x4 acc[R];
 #pragma unroll
     for (int m = 0; m < R; ++m)
@@ -297,12 +313,11 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
         const uint8_t *q = wst[wave] + r * Rows::RS + 4 * g;
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-            const bf16x8 ab = pair_order(av[u]);
-            const f32x4 corr = mfma16(ab, neg136, f32x4{0.f, 0.f, 0.f, 0.f});
+            const bf16x8 ab = as_bf16x8(av[u]);
 #pragma unroll
             for (int m = 0; m < R; ++m) {
                 const uint32_t w = *reinterpret_cast<const uint32_t *>(q + m * 16 * Rows::RS + 16 * u);
-                const f32x4 part = mfma16(ab, unpack_u4_pairs(w ^ 0x88888888u), corr);
+                const f32x4 part = mfma16(ab, unpack_q4_16th(w), f32x4{0.f, 0.f, 0.f, 0.f});
                 const float sv = scale_at(sc[m], u);
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
@@ -318,7 +333,7 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
 #pragma unroll
         for (int m = 0; m < R; ++m)
             if (4 * g + k < n)
-                y[int64_t(4 * g + k) * d + 16 * m] = f32_to_bf16(acc[m][k] * rw[k]);
+                y[int64_t(4 * g + k) * d + 16 * m] = f32_to_bf16((16.0f * acc[m][k]) * rw[k]);
 }
 };
 
