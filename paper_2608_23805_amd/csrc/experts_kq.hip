@@ -845,7 +845,7 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
                 float v[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    v[i] = silu_hw(ldexpf(acc[nb][mb][i], k)) * ldexpf(acc[nb + OB][mb][i], k);
+                    v[i] = silu(ldexpf(acc[nb][mb][i], k)) * ldexpf(acc[nb + OB][mb][i], k);
                 lo[nb] = pack_bf16x2_hw(v[0], v[1]);
                 hi[nb] = pack_bf16x2_hw(v[2], v[3]);
             }

@@ -573,7 +573,7 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
                 float v[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    v[i] = silu_hw(acc[nb][mb][i]) * acc[nb + OB][mb][i];
+                    v[i] = silu(acc[nb][mb][i]) * acc[nb + OB][mb][i];
                 lo[nb] = pack_bf16x2_hw(v[0], v[1]);
                 hi[nb] = pack_bf16x2_hw(v[2], v[3]);
             }
