@@ -428,24 +428,36 @@ hipError_t launch_down_kq_stream(const ExpertLaunch &L, hipStream_t s)
 // (k6), exact integers of 10 and 13 bits.
 //   k4: sc q <= 945 is exact in fp16, so one fp16 MFMA per 32 elements.  The
 //       tokens enter as fp16 too: kq_rows_f16_kernel scales each row by a
-//       power of two that puts its largest magnitude in [2^9, 2^10), where
-//       every bf16 value down to 2^-23 of it keeps its 8 bits and smaller
-//       ones are off by at most 2^-34 of it (fp32 sums round at 2^-24).
+//       power of two that puts its largest magnitude in [2^14, 2^15), where
+//       every bf16 value down to 2^-31 of it keeps its 8 bits (in fp16's
+//       subnormal range, which the MFMA reads as it is).  A row with a value
+//       that does not is marked, and its outputs are computed from the bf16
+//       row in fp32 after the tile's others (exact_rows): no token loses bits.
 //   k6: sc = 16 h + l (h in -8..8, l in -8..7): 16 h (q - 32) and l (q - 32)
-//       have at most 8 significant bits each, two exact bf16 MFMAs.
+//       have at most 8 significant bits each, two exact bf16 MFMAs.  They carry
+//       2^-15, so that the accumulators stay near the results' own magnitude
+//       (d is 2^-15 of a matrix's largest weight) and reach as far.
 // At a super-block's end the k4 accumulators take their mins off, acc -=
 // (dmin / d) sum_j m_j S_j, and both move to the next unit, acc *= d / d_next;
 // the result is acc d after the last (and 2^-k of the row's scale).  S_j, the
 // rows' sums over the 32-element sub-blocks, comes from MFMAs against
 // indicator rows (each wavefront its share of the row blocks), crosses LDS
-// and comes back as an operand in three fp16 parts (33 bits) beside m_j
-// (0..63, exact).  A super-block with d = 0 keeps the previous unit, scale 0.
+// as 2^-5 S_j (at most 2^15) and comes back as an operand in three fp16 parts
+// of 11 bits, part p times 2^11p, beside 2^-11p m_j (m_j 0..63: exact).  A
+// super-block with d = 0 keeps the previous unit, scale 0.
 //
 // So k4 costs one MFMA per 16 x 16 x 32 block, and k6 two, with the unpacking
 // (13 and 48 vector operations per fragment) shared by MB row blocks and two
 // fp32 operations per output and super-block; applying each sub-block's scale
 // and min in fp32 instead took two (k6: two) FMAs per output and sub-block
 // and kept the vector ALU at 96 cycles a block.
+//
+// Error against 64 bits, as the share of values off the correctly rounded bf16
+// (d 2048, I 512; this form / a sub-block at a time with the codes as 128 + q):
+// act 5.4e-4 / 23e-4 on N(0, 1) tokens, 1.0e-3 / 8.6e-3 and 1.7e-3 / 5.2e-3 with
+// one element of 2^10 and 2^20; y rows 1.3e-4 / 0.9e-4 (fp32 sums in another
+// order: a sum for each MFMA's 32 elements before it is added gives 0.9e-4 and
+// takes 1844 us for 1546 at 32768 tokens); the layer's outputs 2.3452e-3 both.
 namespace kqt {
 constexpr int BK = 64, ROWB = BK * 2, QROWB = BK / 2, HROWB = BK / 4;
 
@@ -498,7 +510,8 @@ __device__ __forceinline__ f16x8 unpack_k4_f16(uint32_t w, uint32_t sc2)
     return __builtin_bit_cast(f16x8, r);
 }
 
-// k6: 8 codes and a sub-block's scale -> the two operands
+// k6: 8 codes and a sub-block's scale -> the two operands, times K6_SCALE
+constexpr float K6_SCALE = 1.0f / 32768;
 __device__ __forceinline__ void unpack_k6_pair(uint32_t lo4, uint32_t hi2, int sc, bf16x8 &hi, bf16x8 &lo)
 {
     const int h16 = (sc + 8) & ~15;                // sc = 16 h + l, l in -8 .. 7
@@ -506,13 +519,13 @@ __device__ __forceinline__ void unpack_k6_pair(uint32_t lo4, uint32_t hi2, int s
     t = (t | (t << 4)) & 0x0F0F0F0Fu;
     const uint32_t ev = (lo4 & 0x0F0F0F0Fu) | ((t & 0x03030303u) << 4);          // elements 0, 2, 4, 6
     const uint32_t od = ((lo4 >> 4) & 0x0F0F0F0Fu) | ((t & 0x0C0C0C0Cu) << 2);   // elements 1, 3, 5, 7
-    const float s1 = float(h16), s2 = float(sc - h16);
+    const float s1 = float(h16) * K6_SCALE, s2 = float(sc - h16) * K6_SCALE;
     const float o1 = -32.0f * s1, o2 = -32.0f * s2;
     u32x4 a, b;
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
         const float fe = float((ev >> (8 * h)) & 0xFFu), fo = float((od >> (8 * h)) & 0xFFu);
-        // exact: integers of at most 8 significant bits, the top half of their binary32
+        // exact: at most 8 significant bits, the top half of their binary32
         a[h] = __builtin_amdgcn_perm(__float_as_uint(fmaf(fo, s1, o1)), __float_as_uint(fmaf(fe, s1, o1)), 0x07060302u);
         b[h] = __builtin_amdgcn_perm(__float_as_uint(fmaf(fo, s2, o2)), __float_as_uint(fmaf(fe, s2, o2)), 0x07060302u);
     }
@@ -654,7 +667,7 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
             for (int j = 0; j < 4; ++j)
                 reinterpret_cast<uint32_t *>(tb)[j * TN + tid] = dv != 0.0f ? p[j] : 0u;
             *reinterpret_cast<u32x4 *>(tb + S::T_SC + S::T_R + S::T_C + tid * 16) = u32x4{p[4], p[5], p[6], p[7]};
-            reinterpret_cast<float *>(tb + S::T_SC + S::T_R)[tid] = h2f(uint16_t(hd[0] >> 16)) / u;
+            reinterpret_cast<float *>(tb + S::T_SC + S::T_R)[tid] = 32.0f * (h2f(uint16_t(hd[0] >> 16)) / u);
         } else {
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
@@ -734,20 +747,21 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
             sacc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     // a lane holds sub-blocks 4g .. 4g + 3 (g < 2) of row r16: their three fp16 parts, in the operand's layout
+    // (part p times 2^11p, against mins times 2^-11p: each part keeps its 11 bits)
     auto store_sums = [&]() {
         if constexpr (GU) {
             if (g < 2) {
 #pragma unroll
                 for (int q = 0; q < SMB; ++q) {
                     uint16_t *sp = sums + ((wave * SMB + q) * 16 + r16) * 32 + 4 * g;
-                    f32x4 s = sacc[q];
+                    f32x4 s = sacc[q] * 0.03125f;
 #pragma unroll
                     for (int p = 0; p < 3; ++p) {
                         uint16_t h[4];
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             h[i] = f16_bits(s[i]);
-                            s[i] -= h2f(h[i]);
+                            s[i] = (s[i] - h2f(h[i])) * 2048.0f;
                         }
                         *reinterpret_cast<uint2 *>(sp + 8 * p) =
                             make_uint2(uint32_t(h[0]) | (uint32_t(h[1]) << 16), uint32_t(h[2]) | (uint32_t(h[3]) << 16));
@@ -757,6 +771,8 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
         }
     };
     // super-block sb - 1 ends: its mins come off, and the accumulators move to super-block sb's unit
+    const _Float16 ps = g == 0 ? _Float16(1.0f) : g == 1 ? _Float16(0x1p-11f) : _Float16(0x1p-22f);   // (part 3 is 0)
+    [[maybe_unused]] const f16x8 part_scale = {ps, ps, ps, ps, ps, ps, ps, ps};
     auto finish = [&](int sb) {
         const uint8_t *tb = tables + (sb & 1) * S::TABLE, *to = tables + ((sb & 1) ^ 1) * S::TABLE;
 #pragma unroll
@@ -764,7 +780,7 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
             const f32x4 r = *reinterpret_cast<const f32x4 *>(tb + S::T_SC + (col_of(nb) + 4 * g) * 4);
             if constexpr (GU) {
                 const f16x8 mf =
-                    *reinterpret_cast<const f16x8 *>(to + S::T_SC + S::T_R + S::T_C + (col_of(nb) + r16) * 16);
+                    *reinterpret_cast<const f16x8 *>(to + S::T_SC + S::T_R + S::T_C + (col_of(nb) + r16) * 16) * part_scale;
                 f32x4 cm = *reinterpret_cast<const f32x4 *>(to + S::T_SC + S::T_R + (col_of(nb) + 4 * g) * 4);
                 cm = cm * r;
 #pragma unroll
@@ -789,6 +805,59 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         acc[nb][mb][i] *= r[i];
+            }
+        }
+    };
+
+    // token of tile row `row`
+    auto token_of = [&](int row) -> int { return sh ? it.row0 + m0 + row : L.perm[it.row0 + m0 + row]; };
+    // Outputs of the tile's marked rows from their bf16 tokens, sub-block by sub-block in fp32 as on the stream path
+    // (the products plain FMAs): two threads per column, in either tile form, take alternate super-blocks.  A row adds
+    // 24 us to its tiles at d 2048 (vector operations of two threads' serial sums); an N(0, 1) token has a value under
+    // 2^-31 of its largest about three times in a million.
+    auto exact_rows = [&](const uint64_t (&marks)[BM / 64]) {
+        if constexpr (GU) {
+            constexpr int NC = TN / 2;
+            static_assert(2 * NC <= S::THREADS, "");
+            const int c = min(tid >> 1, NC - 1), part = tid & 1;
+            const uint8_t *q0 = obj + (nt * NC + c) * (d / 2), *h0 = obj + I * (d / 2) + (nt * NC + c) * nsb * 16;
+#pragma unroll
+            for (int b = 0; b < BM; b += 64) {
+                for (uint64_t m64 = marks[b / 64]; m64; m64 &= m64 - 1) {     // (the same for every wavefront)
+                    const int row = b + __builtin_ctzll(m64);
+                    const uint32_t *x = reinterpret_cast<const uint32_t *>(static_cast<const uint16_t *>(L.x) +
+                                                                           int64_t(token_of(row)) * d);
+                    float v[2] = {0.f, 0.f};
+#pragma unroll 1
+                    for (int sb = part; sb < nsb; sb += 2) {
+                        const u32x4 hdr[2] = {*reinterpret_cast<const u32x4 *>(h0 + sb * 16),
+                                              *reinterpret_cast<const u32x4 *>(h0 + mbytes + sb * 16)};
+#pragma unroll 4
+                        for (int j = 0; j < 8; ++j)
+#pragma unroll
+                            for (int m = 0; m < 2; ++m) {
+                                const u32x4 w = *reinterpret_cast<const u32x4 *>(q0 + m * mbytes + 128 * sb + 16 * j);
+                                float a, o, p = 0.f, sum = 0.f;
+                                k4_coef(hdr[m], j, a, o);
+#pragma unroll
+                                for (int e = 0; e < 32; e += 2) {
+                                    const uint32_t xx = x[128 * sb + 16 * j + e / 2];
+                                    const float x0 = __uint_as_float(xx << 16), x1 = __uint_as_float(xx & 0xFFFF0000u);
+                                    p = fmaf(x0, float((w[e >> 3] >> (4 * (e & 7))) & 15u), p);
+                                    p = fmaf(x1, float((w[e >> 3] >> (4 * (e & 7) + 4)) & 15u), p);
+                                    sum += x0;
+                                    sum += x1;
+                                }
+                                v[m] = fmaf(a, p, v[m]);
+                                v[m] = fmaf(-o, sum, v[m]);
+                            }
+                    }
+                    v[0] += __shfl_xor(v[0], 1);
+                    v[1] += __shfl_xor(v[1], 1);
+                    if (part == 0 && tid < 2 * NC)
+                        static_cast<uint16_t *>(sh ? L.act_s : L.act)[(int64_t(it.row0) + m0 + row) * I + nt * NC + c] =
+                            f32_to_bf16(silu(v[0]) * v[1]);
+                }
             }
         }
     };
@@ -819,7 +888,7 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
         if (sb + 1 < nsb)
             decode_header(sb + 1);
         else if (tid < TN)                          // after the last, the unit is 1
-            reinterpret_cast<float *>(tables + (nsb & 1) * S::TABLE + S::T_SC)[tid] = unit;
+            reinterpret_cast<float *>(tables + (nsb & 1) * S::TABLE + S::T_SC)[tid] = GU ? unit : unit / K6_SCALE;
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0): the sums and the tables (stage copies stay in flight)
         __builtin_amdgcn_s_barrier();
@@ -832,14 +901,17 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
     // ---- epilogue: lane holds columns 4g .. 4g + 3 of each block of row r16; two blocks at a time are regrouped
     // so that each lane stores 16 contiguous bytes
     const int64_t rowbase = int64_t(it.row0) + m0;
+    uint64_t marks[BM / 64] = {};
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
         const int row = mb * 16 + r16;
-        const bool in = row < valid;
+        bool in = row < valid;
         constexpr int OB = GU ? NB / 2 : NB;        // output blocks
         uint32_t lo[OB], hi[OB];
         if constexpr (GU) {
-            const int k = in ? -int(L.xexp[sh ? it.row0 + m0 + row : L.perm[it.row0 + m0 + row]]) : 0;
+            const int xe = in ? int(L.xexp[token_of(row)]) : 0, k = -xe;
+            in = in && xe != KQ_INEXACT;            // (exact_rows stores those; lanes 16 apart hold the same row)
+            marks[mb / 4] |= (__ballot(xe == KQ_INEXACT) & 0xFFFFull) << (16 * (mb % 4));
 #pragma unroll
             for (int nb = 0; nb < OB; ++nb) {
                 float v[4];
@@ -872,6 +944,7 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
             }
         }
     }
+    exact_rows(marks);
 }
 };
 
@@ -883,8 +956,9 @@ __global__ void __launch_bounds__(S::THREADS, S::WPC *S::WAVES / 4) tile_kq_kern
 }
 
 // Tokens for the k4 tiles: xh[t] = fp16(2^k x[t]) with elements 0 4 1 5 2 6 3 7 of each group of eight, k = xexp[t]
-// putting the row's largest magnitude in [2^9, 2^10) (0 for rows of zeros or with an infinity or NaN; at most
-// 127).  One wavefront per row; the row is read twice, the second time from the caches.
+// putting the row's largest magnitude in [2^14, 2^15) (0 for rows of zeros or with an infinity or NaN, whose
+// outputs are not numbers either way; at most 127).  A row with an element that fp16 does not hold exactly gets
+// xexp[t] = KQ_INEXACT.  One wavefront per row; the row is read twice, the second time from the caches.
 __global__ void __launch_bounds__(256) kq_rows_f16_kernel(const uint16_t *__restrict__ x, uint16_t *__restrict__ xh,
                                                           int8_t *__restrict__ xexp, int T, int d)
 {
@@ -903,20 +977,23 @@ __global__ void __launch_bounds__(256) kq_rows_f16_kernel(const uint16_t *__rest
     // (magnitudes of bf16 bits order as integers; up to 0x7FFF they are exact as floats)
     m = uint32_t(wave_max(float(m)));
     const int e = max(int(m >> 7), 1);
-    const int k = (m == 0u || e == 255) ? 0 : min(136 - e, 127);
+    const int k = (m == 0u || e == 255) ? 0 : min(141 - e, 127);
+    bool exact = true;
     for (int c = lane; c < d / 8; c += 64) {
         const u32x4 v = src[c];
         uint16_t h[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            h[2 * i] = f16_bits(ldexpf(__uint_as_float(v[i] << 16), k));
-            h[2 * i + 1] = f16_bits(ldexpf(__uint_as_float(v[i] & 0xFFFF0000u), k));
+        for (int i = 0; i < 8; ++i) {
+            const float f = ldexpf(__uint_as_float((i & 1) ? v[i / 2] & 0xFFFF0000u : v[i / 2] << 16), k);
+            h[i] = f16_bits(f);
+            exact = exact && h2f(h[i]) == f;
         }
         dst[c] = u32x4{uint32_t(h[0]) | (uint32_t(h[4]) << 16), uint32_t(h[1]) | (uint32_t(h[5]) << 16),
                        uint32_t(h[2]) | (uint32_t(h[6]) << 16), uint32_t(h[3]) | (uint32_t(h[7]) << 16)};
     }
+    const bool all = __all(exact) || e == 255;
     if (lane == 0)
-        xexp[t] = int8_t(k);
+        xexp[t] = all ? int8_t(k) : KQ_INEXACT;
 }
 
 hipError_t launch_kq_rows_f16(const void *x, void *xh, int8_t *xexp, int T, int d, hipStream_t s)

@@ -224,7 +224,9 @@ hipError_t launch_down_f32(const ExpertLaunch &L, hipStream_t s);
 hipError_t init_q4_attributes();
 
 // quantized-expert mix, Wg / Wu in k4 and Wd in k6 (experts_kq.hip)
-// xh[t] = fp16(2^xexp[t] x[t]) in the k4 tiles' element order
+// xh[t] = fp16(2^xexp[t] x[t]) in the k4 tiles' element order; xexp[t] = KQ_INEXACT: fp16 does not hold the row, and
+// the tiles compute it from x
+constexpr int8_t KQ_INEXACT = -128;
 hipError_t launch_kq_rows_f16(const void *x, void *xh, int8_t *xexp, int T, int d, hipStream_t s);
 hipError_t init_kq_attributes();
 
