@@ -1283,10 +1283,12 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
     const bool has_shared = a->shared_object && T > 0;
     if (has_shared && sched.rounds.empty())
         launches.emplace_back();
-    // The shared expert rides in the first round's launches; in the quantized mix's last, because until its
-    // outputs are written their place (ys) holds the tile path's fp16 tokens.
-    const size_t shared_round = d.wdtype == MSI_W_KQ ? launches.size() - 1 : 0;
-    bool any_tile = false;
+    // The shared expert rides in the first round's launches, beside the later rounds' fills; in the last round's of a
+    // quantized-mix forward with tile items, because until its outputs are written their place (ys) holds the tile
+    // path's fp16 tokens.
+    const bool any_tile = (has_shared && uint32_t(T) > thr) ||
+                          std::any_of(counts.begin(), counts.end(), [&](int32_t c) { return uint32_t(c) > thr; });
+    const size_t shared_round = d.wdtype == MSI_W_KQ && any_tile ? launches.size() - 1 : 0;
     for (size_t r = 0; r < launches.size(); ++r) {
         std::vector<WorkItem> tile_items, stream_items;
         if (r == shared_round && has_shared)
@@ -1297,7 +1299,6 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
                        counts[si.expert], 0};
             (f32 || uint32_t(w.nrows) > thr ? tile_items : stream_items).push_back(w);
         }
-        any_tile |= !tile_items.empty();
         add_launch(r, GU_TILE, tile_items);
         add_launch(r, GU_STREAM, stream_items);      // (empty for f32 layers)
         add_launch(r, DN_TILE, tile_items);
