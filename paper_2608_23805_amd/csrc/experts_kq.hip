@@ -960,8 +960,11 @@ __global__ void __launch_bounds__(S::THREADS, S::WPC *S::WAVES / 4) tile_kq_kern
 // outputs are not numbers either way; at most 127).  A row with an element that fp16 does not hold exactly gets
 // xexp[t] = KQ_INEXACT.  One wavefront per row; the row is read twice, the second time from the caches.
 __global__ void __launch_bounds__(256) kq_rows_f16_kernel(const uint16_t *__restrict__ x, uint16_t *__restrict__ xh,
-                                                          int8_t *__restrict__ xexp, int T, int d)
+                                                          int8_t *__restrict__ xexp, int T, int d,
+                                                          const DevCount *__restrict__ tiles)
 {
+    if (tiles && tiles->n_items == 0)
+        return;                                   // no tile reads the copy
     const int t = int(blockIdx.x) * 4 + int(threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (t >= T)
         return;
@@ -996,12 +999,12 @@ __global__ void __launch_bounds__(256) kq_rows_f16_kernel(const uint16_t *__rest
         xexp[t] = all ? int8_t(k) : KQ_INEXACT;
 }
 
-hipError_t launch_kq_rows_f16(const void *x, void *xh, int8_t *xexp, int T, int d, hipStream_t s)
+hipError_t launch_kq_rows_f16(const void *x, void *xh, int8_t *xexp, int T, int d, const DevCount *tiles, hipStream_t s)
 {
     if (T == 0)
         return hipSuccess;
     launch_k(kq_rows_f16_kernel, unsigned((T + 3) / 4), 256, 0, s, static_cast<const uint16_t *>(x),
-             static_cast<uint16_t *>(xh), xexp, T, d);
+             static_cast<uint16_t *>(xh), xexp, T, d, tiles);
     return hipGetLastError();
 }
 

@@ -227,7 +227,8 @@ hipError_t init_q4_attributes();
 // xh[t] = fp16(2^xexp[t] x[t]) in the k4 tiles' element order; xexp[t] = KQ_INEXACT: fp16 does not hold the row, and
 // the tiles compute it from x
 constexpr int8_t KQ_INEXACT = -128;
-hipError_t launch_kq_rows_f16(const void *x, void *xh, int8_t *xexp, int T, int d, hipStream_t s);
+// (`tiles`: nothing is done if that device-built list is empty; null: always)
+hipError_t launch_kq_rows_f16(const void *x, void *xh, int8_t *xexp, int T, int d, const DevCount *tiles, hipStream_t s);
 hipError_t init_kq_attributes();
 
 // The expert kernels of one storage format: the tile path (rows above the

@@ -1173,8 +1173,9 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
         X.I = I;
         ExpertLaunch GT = X, DT = X, GS = X, DS = X;
         if (d.wdtype == MSI_W_KQ) {
-            HIP_OK(p->timed_launch(MSI_K_PERMUTE, cs,
-                                   [&] { return launch_kq_rows_f16(a->x, B.ys, p->xexp_dev, T, D, cs); }));
+            HIP_OK(p->timed_launch(MSI_K_PERMUTE, cs, [&] {
+                return launch_kq_rows_f16(a->x, B.ys, p->xexp_dev, T, D, p->dcount_dev + 0, cs);
+            }));
             GT.xh = B.ys;
             GT.xexp = p->xexp_dev;
         }
@@ -1313,7 +1314,7 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
     }
     if (any_tile && d.wdtype == MSI_W_KQ)
         HIP_OK(p->timed_launch(MSI_K_PERMUTE, cs,
-                               [&] { return launch_kq_rows_f16(a->x, B.ys, p->xexp_dev, T, D, cs); }));
+                               [&] { return launch_kq_rows_f16(a->x, B.ys, p->xexp_dev, T, D, nullptr, cs); }));
     if (!p->status_clean)
         HIP_OK(launch_clear_word(p->status_dev, cs));
     p->status_clean = false;            // set again below once the word is read back as zero
