@@ -201,8 +201,13 @@ def test_explicit_fill_hit_keeps_generation(li):
     plan.close()
 
 
-def _stale_tile_cell(li, capacity, persistent):
-    """Stale generation on an expert of the tiled MFMA path: the forward
+# tile-path form of the bf16 layers by the mean rows per expert: rows of a tile, columns of a gate/up and a down tile
+FORMS = {"64": (64, 64, 128), "128": (128, 128, 256), "256": (256, 128, 256), "persistent": (256, 128, 256)}
+
+
+def _stale_tile_cell(li, form, device_lists=False):
+    """Stale generation on an expert of the tiled MFMA path, in the given form
+    (from the scheduled forward's lists, or the device-built ones): the forward
     returns MSI_E_STALE with the output untouched, and neither tile kernel
     wrote that expert's rows (its act and y rows keep a canary pattern while
     another tile-path expert's rows are overwritten), so both the gate/up
@@ -212,16 +217,23 @@ def _stale_tile_cell(li, capacity, persistent):
     import paper_2608_23805_amd as msi
     from _gpu_helpers import workspace_parts
     s = li.wl.shape
+    capacity = s.E
     dl = device_layer(li)
     plan = make_plan(li, capacity=capacity)
     ctrl = run_layer(plan, dl)
+    if device_lists:
+        run_layer(plan, dl)                                    # no fill: the next forward takes the device-built lists
     counts, offsets = ctrl["counts"], ctrl["offsets"]
     tile = [e for e in range(s.E) if counts[e] > 16]
-    row_tiles = sum((int(counts[e]) + 255) // 256 for e in tile) + (s.T + 255) // 256
-    down_tiles, gu_tiles = row_tiles * (s.d // 256), row_tiles * (s.I // 128)
-    log(f"stale tile cell: T={s.T} tile experts={len(tile)} gate/up tiles={gu_tiles} down tiles={down_tiles} "
-        f"persistent={persistent}")
-    assert (down_tiles > 256) == persistent and (gu_tiles > 256) == persistent, (gu_tiles, down_tiles)
+    mean = s.T * s.K / s.E
+    assert ("64" if mean <= 48 else "128" if mean <= 112 else "256") == ("256" if form == "persistent" else form)
+    rows_, gu_cols, dn_cols = FORMS[form]
+    row_tiles = sum(-(-int(counts[e]) // rows_) for e in tile) + -(-s.T // rows_)
+    down_tiles, gu_tiles = row_tiles * (s.d // dn_cols), row_tiles * (s.I // gu_cols)
+    log(f"stale tile cell: T={s.T} mean rows={mean:.0f} form={form} tile experts={len(tile)} gate/up tiles={gu_tiles} "
+        f"down tiles={down_tiles}")
+    if form in ("256", "persistent"):                          # (the 256-row down walks more than 256 tiles persistently)
+        assert (down_tiles > 256) == (form == "persistent"), down_tiles
     bad, other = tile[0], tile[-1]
     slot = next(q for q in range(capacity) if plan.query(0, q).expert == bad)
     plan.debug_set_device_gen(0, slot, plan.query(0, slot).generation + 1000)
@@ -254,44 +266,51 @@ def _stale_tile_cell(li, capacity, persistent):
     plan.close()
 
 
-def test_stale_generation_tile_path():
-    """Tile path, down launch under one tile per CU (non-persistent kernel)."""
-    log("cell stale_generation_tile")
-    wl = synth.Workload("cells_tile_bf16", 19, synth.LayerShape(300, 512, 32, 4, 256, "bf16"),
+@pytest.mark.parametrize("form,E,device_lists", [("64", 32, False), ("64", 32, True), ("128", 16, False),
+                                                 ("128", 16, True), ("256", 8, False), ("256", 8, True)])
+def test_stale_generation_tile_path(form, E, device_lists):
+    """Every form of the bf16 tile path but the persistent down kernel (the
+    64-row gate/up tiles of a device-built list run beside the stream list)."""
+    log(f"cell stale_generation_tile {form} device_lists={device_lists}")
+    wl = synth.Workload("cells_tile_bf16", 19, synth.LayerShape(300, 512, E, 4, 256, "bf16"),
                         prior="dirichlet", prior_param=0.5, tau=0.6)
-    _stale_tile_cell(synth.layer_inputs(wl), capacity=32, persistent=False)
+    _stale_tile_cell(synth.layer_inputs(wl), form, device_lists)
 
 
 def test_stale_generation_persistent_tiles():
-    """Prefill-shaped layer whose gate/up and down launches exceed one tile
-    per CU, so both persistent tile kernels run (T = 4096, d = 2048, E = 16,
-    K = 4)."""
+    """Prefill-shaped layer whose down launch exceeds one tile per CU, so the
+    persistent down kernel runs (T = 4096, d = 2048, E = 16, K = 4)."""
     log("cell stale_generation_persistent")
     wl = synth.Workload("cells_persistent_bf16", 20, synth.LayerShape(4096, 2048, 16, 4, 512, "bf16"),
                         prior="dirichlet", prior_param=2.0, tau=0.2)
-    _stale_tile_cell(synth.layer_inputs(wl), capacity=16, persistent=True)
+    _stale_tile_cell(synth.layer_inputs(wl), "persistent")
 
 
 QUANT_CELLS = {
     "q4_T1": ("q4b32", 1), "q4_T300": ("q4b32", 300), "kq_T12": ("kq", 12), "kq_T300": ("kq", 300),
 }
+# more than 64 mean rows per expert: the large tiles
+LARGE_CELLS = {"q4_T300_large": ("q4b32", 300), "kq_T300_large": ("kq", 300)}
 
 
-@pytest.mark.parametrize("cell", sorted(QUANT_CELLS))
+@pytest.mark.parametrize("cell", sorted(QUANT_CELLS) + sorted(LARGE_CELLS))
 def test_stale_generation_quantized(cell):
     """Stale generation on the quantized kernels: the stream kernels of a
     device-built decode list (T = 1: the int4 kernels' token-0 path, whose
     generation compare comes after the work; T = 12 for the 4.5-bit mix) and
-    the tile kernels of a device-built prefill list (T = 300).  The forward
+    the tile kernels of a device-built prefill list (T = 300; the small tiles, 50
+    rows per expert, and the large ones, 150).  The forward
     returns MSI_E_STALE with the output untouched and the stale expert's act
     and y rows unwritten while another expert's rows are overwritten; the
     next forward refills and is exact."""
     import torch
     import paper_2608_23805_amd as msi
     from _gpu_helpers import workspace_parts
-    fmt, T = QUANT_CELLS[cell]
-    wl = synth.Workload(f"cells_{cell}", 40 + sorted(QUANT_CELLS).index(cell),
-                        synth.LayerShape(300, 512, 24, 4, 256, fmt), prior="dirichlet", prior_param=0.5, tau=0.4)
+    large = cell in LARGE_CELLS
+    fmt, T = (LARGE_CELLS if large else QUANT_CELLS)[cell]
+    wid = 51 if large else 40 + sorted(QUANT_CELLS).index(cell)
+    wl = synth.Workload(f"cells_{cell}", wid, synth.LayerShape(300, 512, 8 if large else 24, 4, 256, fmt),
+                        prior="dirichlet", prior_param=0.5, tau=0.4)
     li = synth.layer_inputs(wl)
     s = wl.shape
     log(f"cell stale_generation_quantized {cell}")
