@@ -23,7 +23,6 @@ namespace msi {
 // ============================================================== stream path
 
 namespace stream {
-constexpr int MAXN = 16;        // tokens per expert handled by this path
 constexpr int WAVES = 4;
 constexpr int ROWS = 16;        // weight rows per wavefront
 }  // namespace stream
@@ -266,16 +265,19 @@ __global__ void __launch_bounds__(256, 3) stream_gateup_kernel(ExpertLaunch L)
 // Measured (MI355X, E 512, d 2048, I 512, K 10; direct / staged, us): 2.5 mean
 // rows 141 / 144, 5 161 / 162, 6 167 / 166, 8 178 / 169, 10 186 / 170, 16
 // (half of the experts) 129 / 113; I 768, E 128: 8 rows 34 / 35, 12 35 / 33.
+namespace stream_down {
+constexpr int U = 4, SL = U / 2;
+constexpr int REGION = SL * slab::BYTES;
+constexpr int LDS = stream::WAVES * REGION;       // the wavefronts' weight slabs
+}  // namespace stream_down
+
 template <int NB, bool STAGE>
-struct StreamDown {
-static constexpr int U = 4, SL = U / 2;
-static constexpr int REGION = SL * slab::BYTES;
-static constexpr size_t LDS = stream::WAVES * REGION;
-static constexpr int WAVES_PER_SIMD = 4;
-static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int n_blocks, uint8_t *lds)
+__global__ void __launch_bounds__(256, 4) stream_down_kernel(ExpertLaunch L)
 {
+    using namespace stream_down;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int d = L.d, I = L.I;
-    const StreamTile st = stream_tile(L, d / (stream::WAVES * stream::ROWS), block, n_blocks);
+    const StreamTile st = stream_tile(L, d / (stream::WAVES * stream::ROWS), int(blockIdx.x), int(gridDim.x));
     if (!st.valid)
         return;
     const WorkItem &it = st.it;
@@ -366,14 +368,6 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
             make_uint2(pack_bf16x2(acc[0] * wt, acc[1] * wt), pack_bf16x2(acc[2] * wt, acc[3] * wt));
     }
 }
-};
-
-template <int NB, bool STAGE>
-__global__ void __launch_bounds__(256, 4) stream_down_kernel(ExpertLaunch L)
-{
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    StreamDown<NB, STAGE>::run(L, int(blockIdx.x), int(gridDim.x), lds);
-}
 
 hipError_t launch_gateup_stream(const ExpertLaunch &L, hipStream_t s)
 {
@@ -395,7 +389,7 @@ hipError_t launch_gateup_stream(const ExpertLaunch &L, hipStream_t s)
 template <bool STAGE>
 static hipError_t launch_down(const ExpertLaunch &L, hipStream_t s)
 {
-    const int lds = int(StreamDown<1, STAGE>::LDS) + (STAGE ? 16 * (2 * L.I + 16) : 0);
+    const int lds = stream_down::LDS + (STAGE ? 16 * (2 * L.I + 16) : 0);
     // chunks of NB batches of 128 columns must divide I (I % 128 == 0)
     if (L.I % 512 == 0)
         launch_k(stream_down_kernel<4, STAGE>, L.n_tiles, 256, lds, s, L);
@@ -451,26 +445,11 @@ int tiles_down_f32(int nrows, int d, int I)
     return ((nrows + f32t::ROWS - 1) / f32t::ROWS) * (d / f32t::COLS);
 }
 
-TileGeom geom_gateup_f32(int d, int I)
-{
-    (void)d;
-    return TileGeom{f32t::ROWS, I / f32t::COLS};
-}
-
-TileGeom geom_down_f32(int d, int I)
-{
-    (void)I;
-    return TileGeom{f32t::ROWS, d / f32t::COLS};
-}
-
 __global__ void __launch_bounds__(256) gateup_f32_kernel(ExpertLaunch L)
 {
     __shared__ f32t::Stage<2> lds;
-    int n_items, n_tiles;
-    const int t = launch_tile(L, n_items, n_tiles);
-    if (t < 0)
-        return;                                   // past the device-built list's tiles
-    const WorkItem it = L.items[find_item(L.items, n_items, t)];
+    const int t = xcd_swizzle(int(blockIdx.x), int(gridDim.x));
+    const WorkItem it = L.items[find_item(L.items, L.n_items, t)];
     if (!slot_current(it, L.gen_dev, L.status))
         return;
     const int d = L.d, I = L.I;
@@ -494,11 +473,8 @@ __global__ void __launch_bounds__(256) gateup_f32_kernel(ExpertLaunch L)
 __global__ void __launch_bounds__(256) down_f32_kernel(ExpertLaunch L)
 {
     __shared__ f32t::Stage<1> lds;
-    int n_items, n_tiles;
-    const int t = launch_tile(L, n_items, n_tiles);
-    if (t < 0)
-        return;                                   // past the device-built list's tiles
-    const WorkItem it = L.items[find_item(L.items, n_items, t)];
+    const int t = xcd_swizzle(int(blockIdx.x), int(gridDim.x));
+    const WorkItem it = L.items[find_item(L.items, L.n_items, t)];
     if (!slot_current(it, L.gen_dev, L.status))
         return;
     const int d = L.d, I = L.I;

@@ -285,19 +285,16 @@ __global__ void __launch_bounds__(256, R == 1 ? 3 : 2) stream_gateup_kq_kernel(E
 // with the other half's weight lanes zeroed (lanes with g < 2 carry elements
 // 0 .. 15), each partial scaled by its own d * sc.
 template <int G>
-struct KqStreamDown {
-static constexpr int NB = 8 * G;                       // 32-element blocks per group
-using QL = WaveRows<16 * NB>;                          // 16 bytes of low nibbles per block
-using QH = WaveRows<8 * NB>;                           // 8 bytes of high parts per block
-static constexpr size_t LDS = kqs::WAVES * 16 * (QL::RS + QH::RS);
-static constexpr int WAVES_PER_SIMD = 4;
-static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int n_blocks, uint8_t *lds)
+__global__ void __launch_bounds__(256, 2) stream_down_kq_kernel(ExpertLaunch L)
 {
-    uint8_t (*lst)[16 * QL::RS] = reinterpret_cast<uint8_t (*)[16 * QL::RS]>(lds);
-    uint8_t (*hst)[16 * QH::RS] = reinterpret_cast<uint8_t (*)[16 * QH::RS]>(lds + kqs::WAVES * 16 * QL::RS);
+    constexpr int NB = 8 * G;                          // 32-element blocks per group
+    using QL = WaveRows<16 * NB>;                      // 16 bytes of low nibbles per block
+    using QH = WaveRows<8 * NB>;                       // 8 bytes of high parts per block
+    __shared__ __attribute__((aligned(16))) uint8_t lst[kqs::WAVES][16 * QL::RS];
+    __shared__ __attribute__((aligned(16))) uint8_t hst[kqs::WAVES][16 * QH::RS];
     int t;
     WorkItem it;
-    if (!kq_tile(L, L.d / (kqs::WAVES * kqs::ROWS), block, n_blocks, t, it) || it.nrows == 0 ||
+    if (!kq_tile(L, L.d / (kqs::WAVES * kqs::ROWS), int(blockIdx.x), int(gridDim.x), t, it) || it.nrows == 0 ||
         !slot_current(it, L.gen_dev, L.status))      // nrows 0: unpublished expert, no work
         return;
     const int n = it.nrows, d = L.d, I = L.I, nsb = I / 256;
@@ -365,14 +362,6 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
             y[int64_t(tok) * d] = f32_to_bf16(acc[i] * w);
         }
     }
-}
-};
-
-template <int G>
-__global__ void __launch_bounds__(256, 2) stream_down_kq_kernel(ExpertLaunch L)
-{
-    __shared__ __attribute__((aligned(16))) uint8_t lds[KqStreamDown<G>::LDS];
-    KqStreamDown<G>::run(L, int(blockIdx.x), int(gridDim.x), lds);
 }
 
 namespace {

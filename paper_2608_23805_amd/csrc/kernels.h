@@ -167,12 +167,7 @@ inline hipError_t launch_both(const ExpertLaunch &T, const ExpertLaunch &S, hipS
     constexpr size_t LDS = Tile::LDS > Stream::LDS ? Tile::LDS : Stream::LDS;
     if (!T.dev_n || !S.dev_n || T.n_tiles % 8 != 0)
         return hipErrorInvalidValue;
-    static_assert(LDS <= 80 * 1024, "");
-    if constexpr (LDS > 64 * 1024) {
-        static const hipError_t e = allow_large_lds(reinterpret_cast<const void *>(&both_kernel<Tile, Stream>));
-        if (e != hipSuccess)
-            return e;
-    }
+    static_assert(LDS <= 64 * 1024, "within the default limit of a launch's LDS");
     launch_k(both_kernel<Tile, Stream>, T.n_tiles + S.n_tiles, 256, LDS, s, T, S, T.n_tiles);
     return hipGetLastError();
 }
@@ -247,7 +242,6 @@ struct KernelSet {
     Both gu_both = nullptr, dn_both = nullptr;
 };
 // kernels of a batch of `rows` routed rows (T * K) over E experts
-const KernelSet &q4_kernels(uint64_t rows, uint64_t E);
 const KernelSet &q4_kernels(uint64_t rows, uint64_t E);
 const KernelSet &kq_kernels(uint64_t rows, uint64_t E);
 const KernelSet &bf16_kernels(uint64_t rows, uint64_t E);
