@@ -405,10 +405,14 @@ hipError_t launch_down_stream(const ExpertLaunch &L, hipStream_t s)
     return L.n_tiles == 0 ? hipSuccess : launch_down<false>(L, s);
 }
 
-// staged where the rows leave a CU its four workgroups: 8 KB of weights and 32 I + 256 bytes in 40 KB
+// Staged where it measured faster at every batch past the rule's 8 mean rows: 16 KB of weight slabs and 32 I + 256
+// bytes of rows leave a CU its four workgroups up to I = 640 and three above.  Direct / staged, us (d 2048, K 8, E 256,
+// mean rows 9, 10, 12, 14, 16): I 640 115 / 111, 118 / 111, 114 / 107, 100 / 92, 69 / 64; I 768 134 / 130, 137 / 130,
+// 136 / 126, 119 / 107, 81 / 74; I 896 156 / 156, 158 / 157, 156 / 150, 136 / 129, 92 / 90, but at E 128 78 / 81,
+// 79 / 81, 76 / 74, 66 / 67, 50 / 47 (I 768 there 68 / 67, 68 / 67, 66 / 62, 58 / 54, 43 / 39).
 hipError_t launch_down_stream_staged(const ExpertLaunch &L, hipStream_t s)
 {
-    return L.n_tiles == 0 ? hipSuccess : L.I <= 896 ? launch_down<true>(L, s) : launch_down<false>(L, s);
+    return L.n_tiles == 0 ? hipSuccess : L.I <= 768 ? launch_down<true>(L, s) : launch_down<false>(L, s);
 }
 
 // The 64-row tiles and the stream list in one launch (both_kernel).  Measured

@@ -1,5 +1,5 @@
 """The bf16 stream down kernel reads its act rows directly up to 8 mean rows per
-expert and through LDS past that (where I is at most 896); both are one function:
+expert and through LDS past that (where I is at most 768); both are one function:
 the tokens of a 32-token batch (8 mean rows) give the same bytes in a 33-token
 one where their experts have at most 16 rows (the stream path) or more (the tile
 path) in both, at every chunk width and number of staged pieces I leaves, and the batch
