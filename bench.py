@@ -234,8 +234,8 @@ def bench_prefill(args, cs, side, name="prefill_bf16"):
                          "flops_per_launch": flops_gu, "algorithmic_bytes_per_launch": bytes_gu,
                          "avg_launch_us": round(avg_gu * 1e3, 1),
                          "note": {"q4b32": "int4 weights unpacked to bf16 MFMA operands",
-                                  "kq": "4.5-bit weights unpacked to exact bf16 MFMA operands, per-sub-block "
-                                        "scale and min applied in fp32"}.get(s.wdtype, "")},
+                                  "kq": "4.5-bit weights unpacked to exact fp16 MFMA operands in units of their super-block, "
+                                        "tokens as scaled fp16 (rows it does not hold: fp32), mins and units in fp32"}.get(s.wdtype, "")},
                kernels=kernels, _routed_idx=routed_idx)
     log(f"[bench] prefill: {ms:.3f} ms/step, {res['value']:.0f} tok/s, layer {res['layer_tflops']} TFLOP/s, "
         f"gate/up {avg_gu * 1e3:.0f} us = {achieved:.0f} TFLOP/s")

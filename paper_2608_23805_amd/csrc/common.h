@@ -198,8 +198,8 @@ __device__ __forceinline__ bool slot_gen_ok(const WorkItem &it, uint32_t g, uint
     return false;
 }
 
-// Generation check done by every tile before it reads a slot: true if the
-// slot denotes the version the host scheduled.  A mismatch raises the stale
+// Generation check in front of the work (other kernels read the word early
+// and compare it before their stores, see above): true if the slot denotes the version the host scheduled.  A mismatch raises the stale
 // bit (vector atomic) and the tile must write nothing.
 __device__ __forceinline__ bool slot_current(const WorkItem &it, const uint32_t *gen_dev, uint32_t *status)
 {
@@ -426,7 +426,6 @@ struct WaveRows {
         }
     }
     // write the rows to the wavefront's region (see below for why no wait follows)
-    template <bool HOLD = false>
     __device__ __forceinline__ void store(uint8_t *lds, int lane) const
     {
 #pragma unroll
@@ -436,10 +435,9 @@ struct WaveRows {
                 *reinterpret_cast<u32x4 *>(lds + row * RS + 16 * ch) = v[k];
         }
         // Other lanes wrote what this lane reads next.  Where not every lane stores, one that does not could keep an
-        // earlier chunk's word, as nothing it did itself changed it: there memory is opaque from here on.  HOLD asks
-        // for the same where it pays to have every load of the chunk issued before the first word is read back
-        // (int4: down 75 -> 66 us on a 1013-token batch; the quantized mix, short of registers: 88 -> 106).
-        if constexpr (HOLD || (16 * CPR) % 64 != 0)
+        // earlier chunk's word, as nothing it did itself changed it: there memory is opaque from here on.  (Everywhere
+        // would hold all loads of a chunk in front of it: quantized mix, short of registers, down 88 -> 106 us.)
+        if constexpr ((16 * CPR) % 64 != 0)
             asm volatile("" ::: "memory");
     }
 };

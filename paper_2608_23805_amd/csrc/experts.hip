@@ -3,14 +3,15 @@
 //
 //  * tile path (bf16, > STREAM tokens): tiles.hip.
 //  * stream path (bf16, <= 16 tokens): weight streaming.  The weights are the
-//    MFMA A operand read straight from HBM in the 16x16x32 fragment layout
-//    (each wavefront owns 16 weight rows; each weight byte is read once), the
-//    expert's tokens (at most 16, zero-padded) are the B operand held in LDS.
+//    MFMA A operand, read in whole lines (each wavefront owns 16 weight rows;
+//    each weight byte is read once) and rearranged into 16x16x32 fragments in
+//    the wavefront's LDS slabs; the expert's tokens (at most 16) are the B
+//    operand.
 //  * f32 path (fp32 layers): FMA dot products in fixed sequential order
 //    (dot_f32.h).
 //
-// Every workgroup checks the slot generation first and writes nothing on a
-// mismatch (fail closed).  Outputs: act[row, I] = silu(x Wg^T) * (x Wu^T) and
+// Every workgroup compares the slot generation before its first store and
+// writes nothing on a mismatch (fail closed).  Outputs: act[row, I] = silu(x Wg^T) * (x Wu^T) and
 // y[row, d] = row_weight * (act Wd^T), rows in permuted order, both rounded
 // to bf16 once (fp32 throughout for fp32 layers).
 #include "common.h"

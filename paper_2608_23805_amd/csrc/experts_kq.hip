@@ -22,9 +22,10 @@
 // by zeroing the weight lanes of the other half (lanes 0..31 carry elements
 // 0..15 of the 32).
 //
-//  * stream path (<= 16 tokens per expert): tokens as the A operand and
-//    weights as the B operand, both read straight from memory, so each output
-//    lane holds one weight row (and that row's coefficients) for four tokens;
+//  * stream path (<= 16 tokens per expert): tokens as the A operand, read
+//    straight from memory, and weights as the B operand (WaveRows), so each
+//    output lane holds one weight row (and that row's coefficients) for four
+//    tokens;
 //  * tile path: 64 x 128 or 128 x 256 outputs per workgroup, whole
 //    super-blocks summed in units of their d (described there).
 #include "common.h"
@@ -438,8 +439,8 @@ hipError_t launch_down_kq_stream(const ExpertLaunch &L, hipStream_t s)
 // So k4 costs one MFMA per 16 x 16 x 32 block, and k6 two, with the unpacking
 // (13 and 48 vector operations per fragment) shared by MB row blocks and two
 // fp32 operations per output and super-block; applying each sub-block's scale
-// and min in fp32 instead took two (k6: two) FMAs per output and sub-block
-// and kept the vector ALU at 96 cycles a block.
+// and min in fp32 instead took two FMAs per output and sub-block and kept the
+// vector ALU at 96 cycles a block.
 //
 // Error against 64 bits, as the share of values off the correctly rounded bf16
 // (d 2048, I 512; this form / a sub-block at a time with the codes as 128 + q):
@@ -1030,8 +1031,9 @@ using KqBig = kqt::Shape<GU, 128, 256, 4, 2>;
 // The 64-row gate/up tiles and the stream list in one launch (both_kernel).
 // Measured (MI355X, E 512, d 2048, I 512, K 10, router bias 0.3 ln Zipf(1.5);
 // us): two launches 28 + 83 (128 tokens), 36 + 101 (251), 95 + 121 (1013);
-// together 92, 124, 207.  Down stays in two: the stream kernel runs five
-// workgroups per CU alone, three beside the tiles' LDS (130 against 21 + 88).
+// together 92, 124, 207.  Down stays in two: its stream kernel runs five
+// workgroups per CU alone (96 registers), three in a joint kernel (137, both
+// lists' live together; LDS would leave four): 130 against 21 + 88.
 hipError_t launch_gateup_kq_both(const ExpertLaunch &T, const ExpertLaunch &S, hipStream_t s)
 {
     using Tile = KqTile<KqSmall<true>>;
@@ -1056,14 +1058,14 @@ const KernelSet kq_set{kq_tiles<S<true>>, tiles_gateup_kq_stream<R>, kq_tiles<S<
 // same chain of operations per output), so the choice is the launch's.
 // Measured (MI355X, E 512, d 2048, I 512, K 10; gate/up + down, us):
 //   mean rows   64 x 128   128 x 256   (per-sub-block scaling, 128 x 128)
-//      20       182+135    284+206        526+413
-//      59       300+230    365+275           -
-//      80       443+344    377+284        732+642
-//     640      2431+1917  1906+1534      4134+3573
+//      20       190+140    316+217        526+413
+//      59       318+237    393+277           -
+//      80       462+346    393+279        732+642
+//     640      2559+1920  1998+1503      4134+3573
 const KernelSet &kq_kernels(uint64_t rows, uint64_t E)
 {
-    // (R of the stream gate/up by the routed rows, as for the 4-bit kernels; R = 1, R = 2, us: T 1 9.0, 10.8;
-    // T 4 18.0, 15.1; T 16 33.4, 30.5; T 251 116, 100)
+    // (R of the stream gate/up by the routed rows, as for the 4-bit kernels; router bias 0.3 ln Zipf(1.5), R = 1,
+    // R = 2, us: T 1 9.7, 11.4; T 4 14.2, 15.4; T 16 32.6, 30.6; T 128 93, 85; T 251 114, 103; T 1013 132, 124)
     if (rows < 32)
         return kq_set<KqSmall, 1>;
     return rows <= 64 * E ? kq_set<KqSmall, 2> : kq_set<KqBig, 2>;

@@ -126,9 +126,9 @@ __device__ __forceinline__ float scale_at(const uint32_t *w, int b)
 // 16-byte loads, rearranged in the wavefront's own LDS region).  Blocks go
 // in chunks of CH, each chunk's loads issued before its first MFMA.  The sums
 // are sixteenths (exact: a power of two) until they are whole.  A token
-// fragment is 1 KiB from 16 rows and R = 1 gives it to 512 bytes of codes: the
-// fragment loads, not the codes or the arithmetic, bound the kernel (halving
-// its vector operations alone gained 5%), so launches of many items take R = 2.
+// fragment is 1 KiB from 16 rows, which R = 1 gives to 512 bytes of codes and
+// R = 2 to 1 KiB; alone the two forms stay within 2 us of each other, beside
+// the tile list R = 2 gains 9% (both at q4_kernels).
 template <int CH, int R>
 struct Q4StreamGateUp {
 using Rows = WaveRows<16 * CH>;
@@ -199,7 +199,7 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
         issue(c0);
 #pragma unroll
         for (int m = 0; m < NM; ++m)
-            wr[m].template store<true>(wst[wave] + m * 16 * Rows::RS, lane);
+            wr[m].store(wst[wave] + m * 16 * Rows::RS, lane);
         const uint8_t *q = wst[wave] + r * Rows::RS + 4 * g;
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
@@ -309,7 +309,7 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
             load_scales<CH>(sc[m], sp + int64_t(16 * m) * nblk + b0);
 #pragma unroll
         for (int m = 0; m < R; ++m)
-            wr[m].template store<true>(wst[wave] + m * 16 * Rows::RS, lane);
+            wr[m].store(wst[wave] + m * 16 * Rows::RS, lane);
         const uint8_t *q = wst[wave] + r * Rows::RS + 4 * g;
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
@@ -637,10 +637,11 @@ using Q4Down = q4t::Shape<false, 64, 128, 1, 2, 6>;
 
 // The 64-row gate/up tiles, or the down tiles, and the stream list in one
 // launch (both_kernel).  Measured (MI355X, E 512, d 2048, I 512, K 10, router
-// bias 0.3 ln Zipf(1.5); gate/up, us): two launches 23.5 + 74 (128 tokens),
-// 44 + 107 (509), 95 + 112 (1013); together 83, 147, 196; down 11.5 + 46,
-// 24 + 66, 49 + 69 and 50, 87, 114.  The down tiles take four workgroups per
-// CU here, not six, which is what the stream list's registers allow.
+// bias 0.3 ln Zipf(1.5); gate/up, us): two launches 25 + 79 (128 tokens),
+// 47 + 110 (509), 99 + 112 (1013); together 81, 141, 189; down 15 + 43,
+// 25 + 60, 50 + 62 and 52, 88, 115 (the two launches without the gap between
+// them).  The down tiles take four workgroups per CU here, not six, which is
+// what the stream list's registers allow.
 using Q4DownBoth = q4t::Shape<false, 64, 128, 1, 4, 4>;
 
 static hipError_t launch_gateup_q4_both(const ExpertLaunch &T, const ExpertLaunch &S, hipStream_t s)
@@ -669,18 +670,17 @@ static const KernelSet q4_set{q4_tiles<G>, tiles_gateup_q4_stream<R>, q4_tiles<Q
                               R == 2 && G::BM == 64 ? launch_down_q4_both : nullptr};
 
 // Tile forms by the mean rows per expert, R of the stream kernels by the
-// routed rows, which bound the launch's items: from 32 on its workgroups fill
-// the chip with R = 2 as well.  All forms are bit-identical (the same chain of
-// operations per output), so the choice is the launch's.
-// Measured (MI355X, E 512, d 2048, I 512, K 10, us):
-//   stream gate/up + down, R = 1, R = 2 (in parentheses codes converted one by
-//   one, R = 1): T 1 6.8+5.2, 9.1+6.1 (8.3+5.5); T 4 13.5+9.5, 13.6+9.1
-//   (16.7+9.3); T 16 39.7+25.3, 37.6+21.6 (48.2+29.1); T 1013 129+82, 116+66
-//   (148+91);
-//   tile gate/up 64 x 128, 128 x 128: mean rows 40 282, 401; 80 457, 411; 640
-//   2499, 2305; down 64 x 128 by two wavefronts, 128 x 128: 40 127, 223; 80 227,
-//   241; 640 1279, 1407 (in one form of 128 x 128 with an epilogue through LDS:
-//   394, 425, 2380 and 236, 263, 1475).
+// routed rows, which bound the launch's items: from 32 on, which every batch
+// on the device-built lists of more than 16 tokens has, R = 2.  All forms are
+// bit-identical (the same chain of operations per output), so the choice is
+// the launch's.  Measured (MI355X, E 512, d 2048, I 512, K 10, us):
+//   router bias 0.3 ln Zipf(1.5), stream gate/up + down, R = 1, R = 2: T 1
+//   8.2+5.2, 9.8+6.5; T 2 9.5+6.7, 12+7.8; T 4 13.3+9.4, 15+10; T 6 17+10.5,
+//   15.6+10.4; T 8 19.6+12.6, 21.8+11.6; T 16 27.5+18.4, 28.6+17.0; T 1013
+//   111+78, 112+62, and gate/up in one launch with the tiles 208, 189;
+//   no bias, tile gate/up 64 x 128, 128 x 128: mean rows 20 199, 304; 40 278,
+//   403; 80 447, 409; 640 2465, 2327; down 64 x 128 by two wavefronts 40 127, 80
+//   220, 640 1190 (128 x 128, a form no longer here: 223, 241, 1407).
 const KernelSet &q4_kernels(uint64_t rows, uint64_t E)
 {
     if (rows < 32)

@@ -449,8 +449,9 @@ __global__ void __launch_bounds__(1024) route_small_kernel(const float *__restri
 // weights in registers, all loaded at once.  Latency-bound; measured with the
 // selection's launch (MI355X, E 512, K 10; the three block launches / this
 // one, us): T 257 19.6 / 11.7, 384 20.3 / 13.0, 509 20.4 / 15.0, 768 20.4 /
-// 18.7, 1013 21.6 / 22.4; E 64, K 4: T 400 18.6 / 9.1.  Up to 512 tokens the
-// table of 1024 experts (102 KB) always fits.
+// 18.7, 1013 21.6 / 22.4; E 64, K 4: T 400 18.6 / 9.1.  The two meet between
+// 768 and 1013; the line is drawn short of that, at 512, where a thread's pairs
+// are eight at most and the table of 1024 experts (102 KB) fits.
 constexpr int PERM_ONE_MAX = 512;
 
 static size_t perm_one_lds(int T, int E)
