@@ -426,7 +426,11 @@ hipError_t launch_down_kq_stream(const ExpertLaunch &L, hipStream_t s)
 //   k6: sc = 16 h + l (h in -8..8, l in -8..7): 16 h (q - 32) and l (q - 32)
 //       have at most 8 significant bits each, two exact bf16 MFMAs.  They carry
 //       2^-15, so that the accumulators stay near the results' own magnitude
-//       (d is 2^-15 of a matrix's largest weight) and reach as far.
+//       (d is 2^-15 of a matrix's largest weight) and reach as far.  An MFMA
+//       rounds more than once on its way into its C, so two of them a block
+//       straight into the accumulators lose more than the one FMA a sub-block
+//       they stand for: each stage's 64 elements are summed from zero, the l
+//       parts first, and then added.
 // At a super-block's end the k4 accumulators take their mins off, acc -=
 // (dmin / d) sum_j m_j S_j, and both move to the next unit, acc *= d / d_next;
 // the result is acc d after the last (and 2^-k of the row's scale).  S_j, the
@@ -438,16 +442,17 @@ hipError_t launch_down_kq_stream(const ExpertLaunch &L, hipStream_t s)
 //
 // So k4 costs one MFMA per 16 x 16 x 32 block, and k6 two, with the unpacking
 // (13 and 48 vector operations per fragment) shared by MB row blocks and two
-// fp32 operations per output and super-block; applying each sub-block's scale
-// and min in fp32 instead took two FMAs per output and sub-block and kept the
-// vector ALU at 96 cycles a block.
+// (k6: six) fp32 operations per output and super-block; applying each sub-block's
+// scale and min in fp32 instead took two FMAs per output and sub-block and kept
+// the vector ALU at 96 cycles a block.
 //
 // Error against 64 bits, as the share of values off the correctly rounded bf16
 // (d 2048, I 512; this form / a sub-block at a time with the codes as 128 + q):
 // act 5.4e-4 / 23e-4 on N(0, 1) tokens, 1.0e-3 / 8.6e-3 and 1.7e-3 / 5.2e-3 with
-// one element of 2^10 and 2^20; y rows 1.3e-4 / 0.9e-4 (fp32 sums in another
-// order: a sum for each MFMA's 32 elements before it is added gives 0.9e-4 and
-// takes 1844 us for 1546 at 32768 tokens); the layer's outputs 2.3452e-3 both.
+// one element of 2^10 and 2^20; y rows 7.6e-5 / 8.3e-5 (I 256: 5.8e-5 / 5.9e-5,
+// 768: 8.4e-5 / 10.2e-5).  Straight into the accumulators y rows had 13.0e-5
+// (I 768: 15.7e-5); summed by 32 elements 8.5e-5.  At 32768 tokens down takes
+// 1795 us, by 32 elements 1848, straight 1546 (same card).
 namespace kqt {
 constexpr int BK = 64, ROWB = BK * 2, QROWB = BK / 2, HROWB = BK / 4;
 
@@ -569,21 +574,36 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
     // ---- stage copies (slots permuted as in the 4-bit tiles, so fragment reads are free of bank conflicts)
     [[maybe_unused]] const void *abase = GU ? L.xh
                            : static_cast<const uint8_t *>(sh ? L.act_s : L.act) + (int64_t(it.row0) + m0) * int64_t(I) * 2;
-    uint32_t aoff[S::LA], qoff[S::LQ], hoff = 0;
-#pragma unroll
-    for (int i = 0; i < S::LA; ++i) {
-        const int r = 8 * (WAVES * i + wave) + (lane >> 3);
+    // Offset of copy i.  Down's are worked out again for each stage (the lane index is made opaque): its products' sums
+    // (below) leave no registers to keep them in.
+    auto lane_of = [&]() {
+        int l = lane;
+        if constexpr (!GU)
+            asm volatile("" : "+v"(l));
+        return l;
+    };
+    auto a_off = [&](int i) -> uint32_t {
+        const int l = lane_of(), r = 8 * (WAVES * i + wave) + (l >> 3);
         const int m = m0 + min(r, valid - 1);     // rows past the end repeat the last one and are never stored
         const uint32_t src = !GU ? uint32_t(m - m0) : sh ? uint32_t(it.row0 + m) : uint32_t(L.perm[it.row0 + m]);
-        aoff[i] = src * uint32_t(K * 2) + uint32_t(((lane & 7) ^ ((r >> 1) & 7)) << 4);
-    }
+        return src * uint32_t(K * 2) + uint32_t(((l & 7) ^ ((r >> 1) & 7)) << 4);
+    };
+    auto q_off = [&](int i) -> uint32_t {
+        const int l = lane_of(), c = 32 * (WAVES * i + wave) + (l >> 1);
+        return col_matrix(c) + col_row(c) * uint32_t(K / 2) + uint32_t(16 * ((l & 1) ^ ((c >> 3) & 1)));
+    };
+    auto h_off = [&]() -> uint32_t {
+        return col_matrix(0) + uint32_t(d) * uint32_t(K / 2) + col_row(64 * (wave % S::NH) + lane_of()) * uint32_t(K / 4);
+    };
+    [[maybe_unused]] uint32_t aoff[S::LA], qoff[S::LQ];
+    if constexpr (GU) {
 #pragma unroll
-    for (int i = 0; i < S::LQ; ++i) {
-        const int c = 32 * (WAVES * i + wave) + (lane >> 1);
-        qoff[i] = col_matrix(c) + col_row(c) * uint32_t(K / 2) + uint32_t(16 * ((lane & 1) ^ ((c >> 3) & 1)));
+        for (int i = 0; i < S::LA; ++i)
+            aoff[i] = a_off(i);
+#pragma unroll
+        for (int i = 0; i < S::LQ; ++i)
+            qoff[i] = q_off(i);
     }
-    if (!GU)
-        hoff = col_matrix(0) + uint32_t(d) * uint32_t(K / 2) + col_row(64 * (wave % S::NH) + lane) * uint32_t(K / 4);
     auto issue = [&](int stage, int buf) {
         uint8_t *st = lds8 + buf * STAGE;
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -593,15 +613,15 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
             __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(obj), 0, 0x7fffffff, 0x00020000u);
 #pragma unroll
         for (int i = 0; i < S::LA; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ar, (lds_void_t *)(st + (WAVES * i + wave) * 1024), 16, aoff[i],
-                                                     stage * ROWB, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ar, (lds_void_t *)(st + (WAVES * i + wave) * 1024), 16,
+                                                     GU ? aoff[i] : a_off(i), stage * ROWB, 0, 0);
 #pragma unroll
         for (int i = 0; i < S::LQ; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(wr_, (lds_void_t *)(st + S::A_BYTES + (WAVES * i + wave) * 1024),
-                                                     16, qoff[i], stage * QROWB, 0, 0);
+                                                     16, GU ? qoff[i] : q_off(i), stage * QROWB, 0, 0);
         if (!GU && wave < S::NH)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(wr_, (lds_void_t *)(st + S::A_BYTES + S::Q_BYTES + wave * 1024), 16,
-                                                     hoff, stage * HROWB, 0, 0);
+                                                     h_off(), stage * HROWB, 0, 0);
 #else
         (void)st, (void)stage;
 #endif
@@ -683,50 +703,82 @@ static __device__ __forceinline__ void run(const ExpertLaunch &L, int block, int
     // sub-block sums: this wavefront's share of its row blocks
     constexpr int SMB = GU ? MB / S::WC : 1;
     f32x4 sacc[SMB];
+    auto a_frag = [&](const uint8_t *st, int r, int kb) {     // elements 8g .. 8g + 7 of block kb of row r
+        return *reinterpret_cast<const u32x4 *>(st + r * ROWB + (((4 * kb + g) ^ ((r >> 1) & 7)) << 4));
+    };
+    auto codes = [&](const uint8_t *st, int c, int kb) {      // their codes' (low) nibbles in weight row c
+        return *reinterpret_cast<const uint32_t *>(st + S::A_BYTES + c * QROWB + 16 * (kb ^ ((c >> 3) & 1)) + 4 * g);
+    };
     auto compute = [&](int buf, int stage) {
         const uint8_t *st = lds8 + buf * STAGE;
         const uint8_t *sct = tables + ((stage >> 2) & 1) * S::TABLE;
+        if constexpr (GU) {
 #pragma unroll
-        for (int kb = 0; kb < BK / 32; ++kb) {
-            [[maybe_unused]] const int jb = (stage & 3) * 2 + kb;    // 32-element block of the super-block
-            u32x4 af[MB];
+            for (int kb = 0; kb < BK / 32; ++kb) {
+                const int jb = (stage & 3) * 2 + kb;               // 32-element block of the super-block
+                u32x4 af[MB];
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const int r = mb * 16 + r16;
-                af[mb] = *reinterpret_cast<const u32x4 *>(st + r * ROWB + (((4 * kb + g) ^ ((r >> 1) & 7)) << 4));
-            }
-            if constexpr (GU) {
+                for (int mb = 0; mb < MB; ++mb)
+                    af[mb] = a_frag(st, mb * 16 + r16, kb);
                 const uint32_t one = r16 == jb ? 0x3C003C00u : 0u;
                 const f16x8 ind = __builtin_bit_cast(f16x8, u32x4{one, one, one, one});
 #pragma unroll
-                for (int q = 0; q < SMB; ++q) {
-                    const int r = (wave * SMB + q) * 16 + r16;
-                    const f16x8 a = *reinterpret_cast<const f16x8 *>(st + r * ROWB + (((4 * kb + g) ^ ((r >> 1) & 7)) << 4));
-                    sacc[q] = mfma16h(ind, a, sacc[q]);
-                }
-            }
+                for (int q = 0; q < SMB; ++q)
+                    sacc[q] = mfma16h(ind, __builtin_bit_cast(f16x8, a_frag(st, (wave * SMB + q) * 16 + r16, kb)), sacc[q]);
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int c = col_of(nb) + r16;                    // A fragment: weight row c
-                const uint32_t cw = *reinterpret_cast<const uint32_t *>(st + S::A_BYTES + c * QROWB +
-                                                                        16 * (kb ^ ((c >> 3) & 1)) + 4 * g);
-                if constexpr (GU) {
+                for (int nb = 0; nb < NB; ++nb) {
+                    const int c = col_of(nb) + r16;                // A fragment: weight row c
                     const uint32_t s2 = reinterpret_cast<const uint32_t *>(sct)[(stage & 3) * TN + c];
-                    const f16x8 w = unpack_k4_f16(cw, __builtin_amdgcn_perm(s2, s2, kb ? 0x03020302u : 0x01000100u));
+                    const f16x8 w =
+                        unpack_k4_f16(codes(st, c, kb), __builtin_amdgcn_perm(s2, s2, kb ? 0x03020302u : 0x01000100u));
 #pragma unroll
                     for (int mb = 0; mb < MB; ++mb)
                         acc[nb][mb] = mfma16h(w, __builtin_bit_cast(f16x8, af[mb]), acc[nb][mb]);
-                } else {
+                }
+            }
+        } else {
+            // The stage's 64 elements are summed before they are added, the small parts l first.  (The second block's
+            // act fragments are read again for each column block: held, they would spill.)
+            constexpr int G = 4;                                   // row blocks at a time
+            u32x4 af[MB];
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+                af[mb] = a_frag(st, mb * 16 + r16, 0);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                __builtin_amdgcn_sched_barrier(0);
+                const int c = col_of(nb) + r16;                    // A fragment: weight row c
+                bf16x8 hi[2], lo[2];
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
                     const uint32_t hw = *reinterpret_cast<const uint16_t *>(st + S::A_BYTES + S::Q_BYTES + c * HROWB +
                                                                             8 * kb + 2 * g);
-                    bf16x8 w1, w2;
-                    unpack_k6_pair(cw, hw, int(int8_t(sct[(2 * jb + (g >> 1)) * TN + c])), w1, w2);
+                    const int j16 = ((stage & 3) * 2 + kb) * 2 + (g >> 1);   // 16-element sub-block
+                    unpack_k6_pair(codes(st, c, kb), hw, int(int8_t(sct[j16 * TN + c])), hi[kb], lo[kb]);
+                }
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
-                        acc[nb][mb] = mfma16(w1, as_bf16x8(af[mb]), acc[nb][mb]);
+                for (int m0_ = 0; m0_ < MB; m0_ += G) {
+                    f32x4 part[G];
+                    u32x4 a1[G];
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
-                        acc[nb][mb] = mfma16(w2, as_bf16x8(af[mb]), acc[nb][mb]);
+                    for (int q = 0; q < G; ++q) {
+                        part[q] = mfma16(lo[0], as_bf16x8(af[m0_ + q]), f32x4{0.f, 0.f, 0.f, 0.f});
+                        a1[q] = a_frag(st, (m0_ + q) * 16 + r16, 1);
+                    }
+#pragma unroll
+                    for (int q = 0; q < G; ++q)
+                        part[q] = mfma16(lo[1], as_bf16x8(a1[q]), part[q]);
+#pragma unroll
+                    for (int q = 0; q < G; ++q)
+                        part[q] = mfma16(hi[0], as_bf16x8(af[m0_ + q]), part[q]);
+#pragma unroll
+                    for (int q = 0; q < G; ++q)
+                        part[q] = mfma16(hi[1], as_bf16x8(a1[q]), part[q]);
+#pragma unroll
+                    for (int q = 0; q < G; ++q)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            acc[nb][m0_ + q][i] += part[q][i];
                 }
             }
         }
@@ -1033,7 +1085,8 @@ using KqBig = kqt::Shape<GU, 128, 256, 4, 2>;
 // us): two launches 28 + 83 (128 tokens), 36 + 101 (251), 95 + 121 (1013);
 // together 92, 124, 207.  Down stays in two: its stream kernel runs five
 // workgroups per CU alone (96 registers), three in a joint kernel (137, both
-// lists' live together; LDS would leave four): 130 against 21 + 88.
+// lists' live together; LDS would leave four): 130 against 21 + 88 with tiles
+// that did not sum by stage (24 now).
 hipError_t launch_gateup_kq_both(const ExpertLaunch &T, const ExpertLaunch &S, hipStream_t s)
 {
     using Tile = KqTile<KqSmall<true>>;
@@ -1058,10 +1111,10 @@ const KernelSet kq_set{kq_tiles<S<true>>, tiles_gateup_kq_stream<R>, kq_tiles<S<
 // same chain of operations per output), so the choice is the launch's.
 // Measured (MI355X, E 512, d 2048, I 512, K 10; gate/up + down, us):
 //   mean rows   64 x 128   128 x 256   (per-sub-block scaling, 128 x 128)
-//      20       190+140    316+217        526+413
-//      59       318+237    393+277           -
-//      80       462+346    393+279        732+642
-//     640      2559+1920  1998+1503      4134+3573
+//      20       190+169    316+245        526+413
+//      59       318+285    393+327           -
+//      80       462+407    393+338        732+642
+//     640      2559+2162  1998+1737      4134+3573
 const KernelSet &kq_kernels(uint64_t rows, uint64_t E)
 {
     // (R of the stream gate/up by the routed rows, as for the 4-bit kernels; router bias 0.3 ln Zipf(1.5), R = 1,
