@@ -32,7 +32,7 @@ TileGeom geom_down_tile(int d, int I)
     return TileGeom{ring::TM, d / ring::TN};
 }
 
-// Shapes of the tile path for few rows per expert (kernel_set holds the rule between them and the 256-row
+// Shapes of the tile path for few rows per expert (bf16_kernels holds the rule between them and the 256-row
 // form), and of the router logits.
 using Mid128 = MidShape<128, 256, 2, 4, 3, 1>;
 using Router32 = MidShape<32, 32, 2, 2, 6, 1>;
