@@ -1115,11 +1115,12 @@ const KernelSet kq_set{kq_tiles<S<true>>, tiles_gateup_kq_stream<R>, kq_tiles<S<
 //      59       318+285    393+327           -
 //      80       462+407    393+338        732+642
 //     640      2559+2162  1998+1737      4134+3573
-const KernelSet &kq_kernels(uint64_t rows, uint64_t E)
+const KernelSet &kq_kernels(uint64_t rows, uint64_t E, uint64_t items)
 {
-    // (R of the stream gate/up by the routed rows, as for the 4-bit kernels; router bias 0.3 ln Zipf(1.5), R = 1,
+    // (R of the stream gate/up by the launch's items, as for the 4-bit kernels: E 128, K 4, 16 tokens, 48 slots 166 us a
+    // step, 171 with R = 2; router bias 0.3 ln Zipf(1.5), R = 1,
     // R = 2, us: T 1 9.7, 11.4; T 4 14.2, 15.4; T 16 32.6, 30.6; T 128 93, 85; T 251 114, 103; T 1013 132, 124)
-    if (rows < 32)
+    if (items < 32 && rows <= 64 * E)
         return kq_set<KqSmall, 1>;
     return rows <= 64 * E ? kq_set<KqSmall, 2> : kq_set<KqBig, 2>;
 }

@@ -669,9 +669,12 @@ static const KernelSet q4_set{q4_tiles<G>, tiles_gateup_q4_stream<R>, q4_tiles<Q
                               R == 2 && G::BM == 64 ? launch_gateup_q4_both : nullptr,
                               R == 2 && G::BM == 64 ? launch_down_q4_both : nullptr};
 
-// Tile forms by the mean rows per expert, R of the stream kernels by the
-// routed rows, which bound the launch's items: from 32 on, which every batch
-// on the device-built lists of more than 16 tokens has, R = 2.  All forms are
+// Tile forms by the mean rows per expert, R of the stream kernels by what
+// bounds the launch's items: the routed rows on the device-built lists, the
+// largest round on the scheduled path.  From 32 on R = 2 (every batch of more
+// than 16 tokens and top-2 on the device-built lists); the small rounds of a
+// layer with few slots would leave CUs idle at R = 2 (E 128, K 4, 16 tokens,
+// 48 slots, d 1024, I 768: a step takes 318 us, 329 with R = 2).  All forms are
 // bit-identical (the same chain of operations per output), so the choice is
 // the launch's.  Measured (MI355X, E 512, d 2048, I 512, K 10, us):
 //   router bias 0.3 ln Zipf(1.5), stream gate/up + down, R = 1, R = 2: T 1
@@ -681,9 +684,9 @@ static const KernelSet q4_set{q4_tiles<G>, tiles_gateup_q4_stream<R>, q4_tiles<Q
 //   no bias, tile gate/up 64 x 128, 128 x 128: mean rows 20 199, 304; 40 278,
 //   403; 80 447, 409; 640 2465, 2327; down 64 x 128 by two wavefronts 40 127, 80
 //   220, 640 1190 (128 x 128, a form no longer here: 223, 241, 1407).
-const KernelSet &q4_kernels(uint64_t rows, uint64_t E)
+const KernelSet &q4_kernels(uint64_t rows, uint64_t E, uint64_t items)
 {
-    if (rows < 32)
+    if (items < 32 && rows <= 64 * E)
         return q4_set<Q4GateSmall, 1>;
     return rows <= 64 * E ? q4_set<Q4GateSmall, 2> : q4_set<Q4GateBig, 2>;
 }

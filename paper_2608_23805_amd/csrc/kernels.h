@@ -241,9 +241,9 @@ struct KernelSet {
     using Both = hipError_t (*)(const ExpertLaunch &tile, const ExpertLaunch &stream, hipStream_t s);
     Both gu_both = nullptr, dn_both = nullptr;
 };
-// kernels of a batch of `rows` routed rows (T * K) over E experts
-const KernelSet &q4_kernels(uint64_t rows, uint64_t E);
-const KernelSet &kq_kernels(uint64_t rows, uint64_t E);
+// kernels of a batch of `rows` routed rows (T * K) over E experts, no launch with more than `items` stream items
+const KernelSet &q4_kernels(uint64_t rows, uint64_t E, uint64_t items);
+const KernelSet &kq_kernels(uint64_t rows, uint64_t E, uint64_t items);
 const KernelSet &bf16_kernels(uint64_t rows, uint64_t E);
 
 // ---- combine / publication and slot generation words (combine.hip)

@@ -61,15 +61,16 @@ uint64_t matrix_bytes(uint32_t wdtype, uint64_t rows, uint64_t cols, bool down)
     }
 }
 
-// expert kernels of a storage format, for a batch of `rows` routed rows over E experts
-const KernelSet &kernel_set(uint32_t wdtype, uint64_t rows, uint64_t E)
+// expert kernels of a storage format, for a batch of `rows` routed rows over E experts and launches of at most
+// `items` stream items
+const KernelSet &kernel_set(uint32_t wdtype, uint64_t rows, uint64_t E, uint64_t items)
 {
     static const KernelSet f32{tiles_gateup_f32, nullptr, tiles_down_f32, nullptr, nullptr, nullptr,
                                launch_gateup_f32, nullptr, launch_down_f32, nullptr};
     switch (wdtype) {
     case MSI_W_F32: return f32;
-    case MSI_W_Q4B32: return q4_kernels(rows, E);
-    case MSI_W_KQ: return kq_kernels(rows, E);
+    case MSI_W_Q4B32: return q4_kernels(rows, E, items);
+    case MSI_W_KQ: return kq_kernels(rows, E, items);
     default: return bf16_kernels(rows, E);
     }
 }
@@ -1046,7 +1047,7 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
                                   hipMemcpyHostToDevice, cs));
             p->res_version[L0] = core.layer_version(L0);
         }
-        const KernelSet &ks = kernel_set(d.wdtype, uint64_t(T) * K, E);
+        const KernelSet &ks = kernel_set(d.wdtype, uint64_t(T) * K, E, uint64_t(T) * K);
         const int tpg = ks.tiles_gu_stream(1, D, I);
         const int tpd = ks.tiles_dn_stream(1, D, I);
         const int has_sh = a->shared_object ? 1 : 0;
@@ -1122,7 +1123,7 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
                                   hipMemcpyHostToDevice, cs));
             p->res_version[L0] = core.layer_version(L0);
         }
-        const KernelSet &ks = kernel_set(d.wdtype, uint64_t(T) * K, E);
+        const KernelSet &ks = kernel_set(d.wdtype, uint64_t(T) * K, E, uint64_t(T) * K);
         const int thr = int(g_stream_threshold);
         const int has_sh = a->shared_object ? 1 : 0;
         WorklistArgs W{};
@@ -1259,7 +1260,10 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
     std::vector<std::vector<Launch>> launches(sched.rounds.size());
     std::vector<WorkItem> table;
     const bool f32 = d.wdtype == MSI_W_F32;
-    const KernelSet &ks = kernel_set(d.wdtype, uint64_t(T) * K, E);
+    uint64_t round_items = 0;
+    for (const auto &rd : sched.rounds)
+        round_items = std::max<uint64_t>(round_items, rd.items.size());
+    const KernelSet &ks = kernel_set(d.wdtype, uint64_t(T) * K, E, std::min(uint64_t(T) * K, round_items));
     auto add_launch = [&](size_t r, int kind, const std::vector<WorkItem> &items) {
         if (items.empty())
             return;
