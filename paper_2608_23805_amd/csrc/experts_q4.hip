@@ -670,11 +670,12 @@ static const KernelSet q4_set{q4_tiles<G>, tiles_gateup_q4_stream<R>, q4_tiles<Q
                               R == 2 && G::BM == 64 ? launch_down_q4_both : nullptr};
 
 // Tile forms by the mean rows per expert, R of the stream kernels by what
-// bounds the launch's items: the routed rows on the device-built lists, the
-// largest round on the scheduled path.  From 32 on R = 2 (every batch of more
-// than 16 tokens and top-2 on the device-built lists); the small rounds of a
-// layer with few slots would leave CUs idle at R = 2 (E 128, K 4, 16 tokens,
-// 48 slots, d 1024, I 768: a step takes 318 us, 329 with R = 2).  All forms are
+// bounds the launch's items: the experts and routed rows of a decode, the
+// largest round on the scheduled path; on the device-built lists of more than
+// 16 tokens the routed rows alone (the joint launches are R = 2).  From 32 on
+// R = 2; fewer items leave CUs idle with it: E 128, K 4, 16 tokens, 48 slots,
+// d 1024, I 768 318 us a step, 329 with R = 2; E 8, K 2, d 2048, I 4096 resident
+// 88 against 96.  All forms are
 // bit-identical (the same chain of operations per output), so the choice is
 // the launch's.  Measured (MI355X, E 512, d 2048, I 512, K 10, us):
 //   router bias 0.3 ln Zipf(1.5), stream gate/up + down, R = 1, R = 2: T 1

@@ -1047,7 +1047,7 @@ static msi_status forward_impl(msi_plan *p, const msi_forward_args *a, const Fwd
                                   hipMemcpyHostToDevice, cs));
             p->res_version[L0] = core.layer_version(L0);
         }
-        const KernelSet &ks = kernel_set(d.wdtype, uint64_t(T) * K, E, uint64_t(T) * K);
+        const KernelSet &ks = kernel_set(d.wdtype, uint64_t(T) * K, E, std::min(T * K, E));
         const int tpg = ks.tiles_gu_stream(1, D, I);
         const int tpd = ks.tiles_dn_stream(1, D, I);
         const int has_sh = a->shared_object ? 1 : 0;
