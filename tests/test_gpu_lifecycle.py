@@ -291,13 +291,16 @@ QUANT_CELLS = {
 }
 # more than 64 mean rows per expert: the large tiles
 LARGE_CELLS = {"q4_T300_large": ("q4b32", 300), "kq_T300_large": ("kq", 300)}
+# 32 experts and rows or more: 32 weight rows per wavefront of the stream kernels
+WIDE_CELLS = {"q4_T12_wide": ("q4b32", 12), "kq_T12_wide": ("kq", 12)}
 
 
-@pytest.mark.parametrize("cell", sorted(QUANT_CELLS) + sorted(LARGE_CELLS))
+@pytest.mark.parametrize("cell", sorted(QUANT_CELLS) + sorted(LARGE_CELLS) + sorted(WIDE_CELLS))
 def test_stale_generation_quantized(cell):
     """Stale generation on the quantized kernels: the stream kernels of a
     device-built decode list (T = 1: the int4 kernels' token-0 path, whose
-    generation compare comes after the work; T = 12 for the 4.5-bit mix) and
+    generation compare comes after the work; T = 12 for the 4.5-bit mix, and
+    for both formats in the wide form) and
     the tile kernels of a device-built prefill list (T = 300; the small tiles, 50
     rows per expert, and the large ones, 150).  The forward
     returns MSI_E_STALE with the output untouched and the stale expert's act
@@ -306,10 +309,10 @@ def test_stale_generation_quantized(cell):
     import torch
     import paper_2608_23805_amd as msi
     from _gpu_helpers import workspace_parts
-    large = cell in LARGE_CELLS
-    fmt, T = (LARGE_CELLS if large else QUANT_CELLS)[cell]
-    wid = 51 if large else 40 + sorted(QUANT_CELLS).index(cell)
-    wl = synth.Workload(f"cells_{cell}", wid, synth.LayerShape(300, 512, 8 if large else 24, 4, 256, fmt),
+    large, wide = cell in LARGE_CELLS, cell in WIDE_CELLS
+    fmt, T = (LARGE_CELLS if large else WIDE_CELLS if wide else QUANT_CELLS)[cell]
+    wid = 51 if large else 52 if wide else 40 + sorted(QUANT_CELLS).index(cell)
+    wl = synth.Workload(f"cells_{cell}", wid, synth.LayerShape(300, 512, 8 if large else 40 if wide else 24, 4, 256, fmt),
                         prior="dirichlet", prior_param=0.5, tau=0.4)
     li = synth.layer_inputs(wl)
     s = wl.shape

@@ -14,11 +14,11 @@ from _gpu_helpers import device_layer, log, make_plan, run_layer
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,I", [(256, 128), (1024, 256)])
-def test_token_range_q4(d, I):
+@pytest.mark.parametrize("d,I,E", [(256, 128, 12), (1024, 256, 12), (1024, 256, 40)])     # 16 weight rows, 32
+def test_token_range_q4(d, I, E):
     import torch  # noqa: F401  (loads its HIP runtime before the library)
     import oracle
-    wl = synth.Workload("token_range", 47, synth.LayerShape(16, d, 12, 4, I, "q4b32"))
+    wl = synth.Workload("token_range", 47, synth.LayerShape(16, d, E, 4, I, "q4b32"))
     li = synth.layer_inputs(wl)
     s = wl.shape
     x = synth.bf16_bits_to_f32(li.x)
@@ -39,7 +39,7 @@ def test_token_range_q4(d, I):
     assert den.min() > 2.0 ** 90 and den.max() < 2.0 ** 120
     dl = device_layer(li)
     plan = make_plan(li, capacity=s.E)
-    for T in (16, 7, 1):                                # 32 rows and more, fewer, and the one-token form
+    for T in (16, 7, 1):                                # (40 experts: 32 weight rows at 16 tokens)
         for again in range(3):                          # the last runs on a device-built list
             log(f"case token_range d={d} I={I} T={T} call {again}")
             out = run_layer(plan, dl, T=T)["out"].cpu().numpy()
